@@ -202,7 +202,8 @@ def _batch_shapes(c):
 
 def _context(c):
     ctx = ngf.Context(alpha=c["alpha"], tau=c["eps"], rho=c["eps"], levels=c["levels"],
-                      ratio=c["ratio"], max_iter=c["iters"] or 50, lbfgs_mem=5, tol_J=1e-6, early_stop=False)
+                      ratio=c["ratio"], max_iter=c["iters"] or 50, lbfgs_mem=5,
+                      early_stop=False)
     if c["nx"]:
         ctx.set_node_grid((c["nx"], c["ny"], c["nz"]))
     return ctx
