@@ -7,19 +7,32 @@
 // for the warped template, one for v) plus four planes per chunk, instead of
 // in all three directions.
 //
-// Per step k (plane p_w = x0 - 2 + k enters):
-//   W  warp plane p_w (tile + in-plane halo 2); stage R of plane p_w - 1
-//   V  NGF on plane p_v = p_w - 1 (tile + in-plane face halo 1): D term, v
-//   E  adjoint on plane p_e = p_w - 2 (tile): e = G^T v, dD/dy_hat = e dT
-//   Z  P^T along z of plane p_e
-//   Y  P^T along y, then along x into two register accumulators (the two
-//      node planes the image plane touches); build the x-interpolated node
-//      plane used by the next W
+// Per step (plane p_w enters), everything read from LDS was written in an
+// earlier step, so one barrier a step suffices:
+//   W  P and the warp of plane p_w on the tile, and on the in-plane halo where
+//      a later stage reads it; R of the plane beside it
+//   V  NGF on plane p_v = p_w - 1: D term, v.  Differences along x, and along
+//      y within a thread's pair of rows, are between its own registers
+//   E  adjoint on plane p_e = p_w - 2: e = G^T v, dD/dy_hat = e dT, and P^T
+//      along y (the pair) and x (two node planes' accumulators) in registers
+//   a completed node plane: P^T along z over neighbouring lanes, into LDS; a
+//      step later its nodes are summed and stored
 // Ghost planes of the x adjoint stencil (x = -1, x = m_x) are not computed:
 // E substitutes v_x(-1) = -v_x(0) and v_x(m_x) = -v_x(m_x - 1) directly.
 //
 // The P^T partial sums are written in the tile layout the node pass reads:
 // tile (chunk, ty, tz) owns node block [x0/R, x0/R + CX/R] x [...] x [...].
+//
+// What bounds it: vector instruction issue (76 % of the cycles at 256^3), of
+// which the float64 P and template index are the largest part.  Two rows of
+// one node cell a thread share the z interpolations of P (21 float64
+// instructions a pair instead of 36), half the y neighbours and the y part of
+// P^T; the halo's positions and offsets stay packed in registers; values are
+// settled where they are formed so that 127 registers suffice without spills
+// (four waves per SIMD).  256^3, ratio 2, per launch: 162 us, 235 instructions
+// a voxel, against 233 us and 317 for the five-stage form with one voxel's
+// halves in different barriers that this replaced (ratio 4: 220 -> 140 us;
+// spacing 0.9: 253 -> 168 us).
 #include "ngf_internal.h"
 
 #include <math.h>
@@ -53,44 +66,36 @@ __device__ inline double wave_sum(double v) {
     return v;
 }
 
-// threads of the marching workgroup: 256 (512 for the 32 x 32 tile, so that
-// every thread keeps two voxels of a plane)
-template <int TY, int TZ>
-constexpr int march_threads() {
-    return TY == 32 && TZ == 32 ? 512 : kThreads;
-}
-
+// TY x TZ: the (y, z) tile of a workgroup.  Thread t owns the two voxels
+// (2 (t / TZ), t % TZ) and (2 (t / TZ) + 1, t % TZ) of every plane: a pair of
+// rows lies in one node cell along y, so the pair shares its interpolation
+// along z, its neighbour along y is in the thread's own registers, and the y
+// part of P^T is a sum of two registers.
 template <int TY, int TZ, int R>
 struct March {
-    static constexpr int NT = march_threads<TY, TZ>();
+    static constexpr int NT = TY * TZ / 2;
     static constexpr int H2Y = TY + 4, H2Z = TZ + 4, NH2 = H2Y * H2Z;
-    static constexpr int H1Y = TY + 2, H1Z = TZ + 2;
-    static constexpr int NI = TY * TZ, KP = NI / NT;
-    static constexpr int NRING2 = NH2 - NI;             // in-plane halo-2 ring
-    static constexpr int NRING1 = 2 * TZ + 2 * TY;      // in-plane face halo-1 ring
+    static constexpr int NFACE = 2 * (TY + TZ);  // faces of the one-voxel halo
+    static constexpr int NRING = 2 * NFACE + 4;  // every halo position a stencil reads
     static constexpr int BY = TY / R, BZ = TZ / R, PY = BY + 1, PZ = BZ + 1;
-    static constexpr int NOUT = 3 * PY * PZ, KO = (NOUT + NT - 1) / NT;
-    static constexpr int NQY = TY / R + 4, NQZ = TZ / R + 4, NQ = NQY * NQZ;
-    static constexpr int GZ = 3 * TY * PZ;
-    // LDS layout (floats)
-    static constexpr int OFF_TY = 0;                          // 3 x NH2
-    static constexpr int OFF_R = OFF_TY + 3 * NH2;            // NH2
-    static constexpr int OFF_VX = OFF_R + NH2;                // 3 x NI
-    static constexpr int OFF_VY = OFF_VX + 3 * NI;            // 2 x H1Y x TZ
-    static constexpr int OFF_VZ = OFF_VY + 2 * H1Y * TZ;      // 2 x TY x H1Z
-    static constexpr int OFF_G = OFF_VZ + 2 * TY * H1Z;       // max(3 NI, 2 x 3 NQ): sG or Q
-    static constexpr int SZ_G = (3 * NI > 6 * NQ ? 3 * NI : 6 * NQ);
-    static constexpr int OFF_GZ = OFF_G + SZ_G;               // GZ
-    static constexpr int LDS_FLOATS = OFF_GZ + GZ;
-    static_assert(NI % NT == 0, "tile plane must be a multiple of the workgroup");
-    static_assert(TY % R == 0 && TZ % R == 0, "ratio-aligned tile");
-    static_assert((OFF_G % 2) == 0, "double alignment of Q");
-    static_assert(NRING1 <= NT, "face ring in one pass");
-    static_assert(LDS_FLOATS * 4 <= 81920, "two workgroups per CU");
+    static constexpr int NQY = TY / R + 3, NQZ = TZ / R + 3, NQ = NQY * NQZ;
+    static constexpr int KQ = (3 * NQ + NT - 1) / NT;
+    static constexpr int VYS = (TY + 2) * TZ, VZS = TY * (TZ + 2);
+    // LDS layout (floats); the node planes hold doubles and come first
+    static constexpr int OFF_TY = 12 * NQ;          // after 2 x 3 NQ doubles: 2 x NH2
+    static constexpr int OFF_R = OFF_TY + 2 * NH2;  // 2 x NH2
+    static constexpr int OFF_VY = OFF_R + 2 * NH2;  // 2 x VYS (gradient form only from here)
+    static constexpr int OFF_VZ = OFF_VY + 2 * VYS; // 2 x VZS
+    static constexpr int OFF_G = OFF_VZ + 2 * VZS;  // 6 x NT
+    static constexpr int LDS_VALUE = OFF_VY, LDS_GRAD = OFF_G + 6 * NT;
+    static_assert(TY % 4 == 0 && TZ % 4 == 0 && NT % 64 == 0, "pairs of rows, quads of columns");
+    static_assert(TY % R == 0 && TZ % R == 0 && (R == 2 || R == 4), "ratio-aligned tile");
+    static_assert(NRING <= NT && PY * PZ <= NT, "one halo position, one node a thread");
+    static_assert((LDS_GRAD * 4 + 128) * (1024 / NT) <= 163840, "four waves per SIMD");
 };
 
-// image index -> node index and the two weights along one axis, for a
-// power-of-two ratio: voxel i = q R + k lies at node coordinate q + (2k+1)/(2R)
+// Image index -> lower node and upper weight along one axis, for a ratio of 2
+// or 4: voxel i = q R + k lies at node coordinate q + (2k+1)/(2R).
 template <int R>
 __device__ inline int node_of(int i) {
     return i / R;
@@ -99,37 +104,115 @@ template <int R>
 __device__ inline float w1_of(int i) {
     return static_cast<float>(2 * (i % R) + 1) * (0.5f / R);
 }
+// the same of a uniform index, by scalar selection
+template <int R>
+__device__ inline double w1_uniform(int i) {
+    if constexpr (R == 2)
+        return (i & 1) ? 0.75 : 0.25;
+    else
+        return (i & 2) ? ((i & 1) ? 0.875 : 0.625) : ((i & 1) ? 0.375 : 0.125);
+}
 
-// position of face-halo ring entry s (< 2 TZ + 2 TY) in the one-voxel halo box
+// Halo position s (< NRING) in the two-voxel box: the faces of the one-voxel
+// halo (y faces, then z faces), the faces of the two-voxel halo, then the four
+// corners of the one-voxel halo.
 template <int TY, int TZ>
-__device__ inline void ring1_pos_t(int s, int& b1y, int& b1z) {
-    if (s < 2 * TZ) {
-        b1y = s < TZ ? 0 : TY + 1;
-        b1z = 1 + (s % TZ);
+__device__ inline void ring_pos(int s, int& by, int& bz) {
+    using L = March<TY, TZ, 2>;
+    const bool outer = s >= L::NFACE;
+    const int o = outer ? s - L::NFACE : s;
+    const int e = outer ? 1 : 0;
+    if (o < 2 * TZ) {
+        by = o < TZ ? 1 - e : TY + 2 + e;
+        bz = 2 + o % TZ;
+    } else if (o < L::NFACE) {
+        const int q = o - 2 * TZ;
+        by = 2 + (q >> 1);
+        bz = (q & 1) ? TZ + 2 + e : 1 - e;
     } else {
-        const int q = s - 2 * TZ;
-        b1y = 1 + (q >> 1);
-        b1z = (q & 1) ? TZ + 1 : 0;
+        const int q = o - L::NFACE;
+        by = (q & 1) ? TY + 2 : 1;
+        bz = (q & 2) ? TZ + 2 : 1;
+    }
+}
+
+// A value that is the same in every lane, in a scalar register.
+__device__ inline float uniform(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+// Truncation to an integer, saturating, a NaN to 0 (a C++ cast leaves what does
+// not fit undefined).
+__device__ inline int to_int(double v) {
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(v));
+    return i;
+}
+
+// Fixes where v is computed: without it the compiler sinks what forms dT into
+// the stage that uses it two planes later and carries its many operands over.
+__device__ inline void settle(float& v) { asm volatile("" : "+v"(v)); }
+
+__device__ inline bool settle_and(bool u, bool v) {
+    uint64_t m = __builtin_amdgcn_ballot_w64(u) & __builtin_amdgcn_ballot_w64(v);
+    asm volatile("" : "+s"(m));
+    return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+
+template <int CTRL>
+__device__ inline float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// Sum along z of a node cell's voxels (neighbouring lanes), weighted for the
+// cell's lower node on the first lane of the cell and for its upper node on
+// the second.
+template <int R>
+__device__ inline float cell_sum_z(float v, float w0, float w1) {
+    if constexpr (R == 2) {
+        // lane 0: 3/4 own + 1/4 other; lane 1, for the upper node: the same
+        return fmaf(0.25f, dpp<0xB1>(v), 0.75f * v);
+    } else {
+        float lo = w0 * v, hi = w1 * v;
+        lo += dpp<0xB1>(lo);
+        lo += dpp<0x4E>(lo);
+        hi += dpp<0xB1>(hi);
+        hi += dpp<0x4E>(hi);
+        return (threadIdx.x & 1) ? hi : lo;
+    }
+}
+
+// Continuous template index along one axis, yh / h - 1/2.  A power-of-two
+// spacing has an exact reciprocal; any other takes the product with the
+// rounded one and a correction by the remainder, which makes the quotient
+// exact whenever it is representable and its error at most an ulp otherwise.
+template <bool POW2>
+__device__ inline double index_of(double yh, double h, double ih) {
+    if constexpr (POW2) {
+        return fma(yh, ih, -0.5);
+    } else {
+        const double a = fmin(fmax(yh, -1e300), 1e300);  // an infinity would make the remainder NaN
+        const double q = a * ih;
+        return fma(fma(-q, h, a), ih, q) - 0.5;
     }
 }
 
 template <int TY, int TZ, int R, bool GRAD, bool POW2>
 __device__ __forceinline__ void march_body(const ImagePassArgs& a, int CX, int block) {
     using L = March<TY, TZ, R>;
-    constexpr int NT = L::NT;
-    auto ring1_pos = [](int s, int& b1y, int& b1z) { ring1_pos_t<TY, TZ>(s, b1y, b1z); };
+    constexpr int NT = L::NT, H2Z = L::H2Z;
+    constexpr int LEAD = GRAD ? 2 : 1;  // planes before (and after) the chunk a stencil reads
     extern __shared__ float smem[];
+    double* sQ = reinterpret_cast<double*>(smem);
     float* sTy = smem + L::OFF_TY;
     float* sR = smem + L::OFF_R;
-    float* sVx = smem + L::OFF_VX;
     float* sVy = smem + L::OFF_VY;
     float* sVz = smem + L::OFF_VZ;
     float* sG = smem + L::OFF_G;
-    double* sQ = reinterpret_cast<double*>(smem + L::OFF_G);
-    float* sGz = smem + L::OFF_GZ;
     __shared__ double red[NT / 64];
 
     // tile decode, spread over the XCDs so that neighbouring tiles share an L2
+    const int t = threadIdx.x;
     const int tile = xcd_tile(block, a.ntx * a.nty * a.ntz);
     const int tz = tile % a.ntz;
     const int ty = (tile / a.ntz) % a.nty;
@@ -139,413 +222,446 @@ __device__ __forceinline__ void march_body(const ImagePassArgs& a, int CX, int b
     const int sxT = my * mz;
     const int nnod = a.nx * a.ny * a.nz;
     const int qly = max(y0 - 2, 0) / R, qlz = max(z0 - 2, 0) / R;
-    const int jx_first = x0 / R;
     const int xend = min(x0 + CX, mx);  // first plane past the chunk (in the domain)
-    const uint32_t nbytes = static_cast<uint32_t>(mx) * static_cast<uint32_t>(sxT) * 4u;
-    const __amdgpu_buffer_rsrc_t rT = make_rsrc(a.T, nbytes), rR = make_rsrc(a.R, nbytes);
+    const uint32_t plane4 = static_cast<uint32_t>(sxT) * 4u, row4 = static_cast<uint32_t>(mz) * 4u;
+    const uint32_t nplane4 = static_cast<uint32_t>(a.ny * a.nz) * 4u;
+    const __amdgpu_buffer_rsrc_t rT = make_rsrc(a.T, static_cast<uint32_t>(mx) * plane4);
+    const __amdgpu_buffer_rsrc_t rR = make_rsrc(a.R, static_cast<uint32_t>(mx) * plane4);
     const __amdgpu_buffer_rsrc_t rY = make_rsrc(a.y, 3u * static_cast<uint32_t>(nnod) * 4u);
-    const uint32_t plane4 = static_cast<uint32_t>(sxT) * 4u;  // bytes per image plane
-    // steps: the chunk's planes plus two lead-in and two lead-out planes; a
-    // chunk cut short by the domain stops after its last plane
-    const int nstep = xend - x0 + 4;
 
-    // x-interpolated node plane for image plane p (clamped), float64, into sQ.
-    // The node values are loaded into registers one phase ahead of the store
-    // (load_q during the warp phase, store_q after the last read of sG), so
-    // their latency overlaps the warp's gathers.
-    constexpr int KQ = (3 * L::NQ + NT - 1) / NT;
-    float qv0[KQ], qv1[KQ];
-    auto load_q = [&](int p) {
-        const int pc = clampi(p, 0, mx - 1);
-        const int jx = node_of<R>(pc);
+    // uniform operands, in scalar registers
+    const float tau2 = uniform(a.tau * a.tau), rho2 = uniform(a.rho * a.rho);
+    const float taurho = uniform(a.tau * a.rho), nhbar = uniform(-a.hbar);
+
+    // ---- this thread's positions: tile voxels A and B, halo position C ----
+    // A and B.  Where the tile ends outside the domain (ragged), threads there
+    // compute values nobody reads and write nothing; the last rows and columns
+    // inside write the replicated ghosts beside them.
+    const int lz = t % TZ, ly = 2 * (t / TZ);
+    const bool ragged = y0 + TY > my || z0 + TZ > mz;
+    const bool inside = y0 + ly < my && z0 + lz < mz;  // both rows, or neither
+    const bool row_end = ragged && inside && y0 + ly + 2 == my && ly + 2 < TY;
+    const bool col_end = ragged && inside && z0 + lz + 1 == mz && lz + 1 < TZ;
+    const int box = (ly + 2) * H2Z + lz + 2;  // place of A in the two-voxel box, B a row on
+    const uint32_t offA = static_cast<uint32_t>(min(y0 + ly, my - 1) * mz + min(z0 + lz, mz - 1)) * 4u;
+    const int qA = 3 * (((y0 + min(ly, my - 1 - y0)) / R - qly) * L::NQZ +
+                        ((z0 + min(lz, mz - 1 - z0)) / R - qlz));
+    const float wyA = R == 2 ? 0.25f : ((ly & 2) ? 0.625f : 0.125f), wyB = wyA + 1.0f / R;
+    const float wz = w1_of<R>(lz);
+    double dwA = wyA, dwB = wyB;
+    if (R == 2) asm volatile("" : "+s"(dwA), "+s"(dwB));
+    // C, clamped into the domain (the value of a ghost is its voxel's): its
+    // place in the box and its voxel's, its image offset, Q offset and weights
+    // and the slot its v_y or v_z goes to
+    int byC, bzC;
+    ring_pos<TY, TZ>(min(t, L::NRING - 1), byC, bzC);
+    const int cyC = clampi(y0 - 2 + byC, 0, my - 1), czC = clampi(z0 - 2 + bzC, 0, mz - 1);
+    const uint32_t offC = static_cast<uint32_t>(cyC * mz + czC) * 4u;
+    float wyC = w1_of<R>(cyC), wzC = w1_of<R>(czC);
+    const bool face = t < L::NFACE, yface = t < 2 * TZ;
+    const bool flipC = yface ? cyC != y0 - 2 + byC : czC != z0 - 2 + bzC;
+    uint32_t packC1 = static_cast<uint32_t>(byC * H2Z + bzC) |
+                      static_cast<uint32_t>((cyC - y0 + 2) * H2Z + (czC - z0 + 2)) << 16;
+    uint32_t packC2 = static_cast<uint32_t>(3 * ((cyC / R - qly) * L::NQZ + (czC / R - qlz))) |
+                      static_cast<uint32_t>(yface ? (byC - 1) * TZ + (bzC - 2)
+                                                  : (byC - 2) * (TZ + 2) + (bzC - 1))
+                          << 16;
+
+    // ---- node plane of P: x-interpolated nodes of one image plane ----------
+    uint32_t qo[L::KQ];
 #pragma unroll
-        for (int k = 0; k < KQ; ++k) {
-            const int i = threadIdx.x + k * NT;
-            if (i < 3 * L::NQ) {
-                const int c = i / L::NQ;
-                const int r = i - c * L::NQ;
-                const int qz = r % L::NQZ, qy = r / L::NQZ;
-                const int gy = min(qly + qy, a.ny - 1), gz = min(qlz + qz, a.nz - 1);
-                const uint32_t off = static_cast<uint32_t>(c * nnod + gy * a.nz + gz) * 4u;
-                const uint32_t nplane4 = static_cast<uint32_t>(a.ny * a.nz) * 4u;
-                qv0[k] = bload(rY, off, static_cast<uint32_t>(jx) * nplane4);
-                qv1[k] = bload(rY, off, static_cast<uint32_t>(jx + 1) * nplane4);
-            }
+    for (int k = 0; k < L::KQ; ++k) {
+        const int i = min(t + k * NT, 3 * L::NQ - 1);
+        const int r = i / 3, c = i - 3 * r;
+        const int gy = min(qly + r / L::NQZ, a.ny - 1), gz = min(qlz + r % L::NQZ, a.nz - 1);
+        qo[k] = static_cast<uint32_t>(c * nnod + gy * a.nz + gz) * 4u;
+    }
+    auto load_q = [&](int p, float (&q0)[L::KQ], float (&q1)[L::KQ]) {
+        const uint32_t j = static_cast<uint32_t>(node_of<R>(clampi(p, 0, mx - 1))) * nplane4;
+#pragma unroll
+        for (int k = 0; k < L::KQ; ++k) {
+            q0[k] = bload(rY, qo[k], j);
+            q1[k] = bload(rY, qo[k], j + nplane4);
         }
     };
-    auto store_q = [&](int p) {
+    auto store_q = [&](int p, int slot, const float (&q0)[L::KQ], const float (&q1)[L::KQ]) {
         const int pc = clampi(p, 0, mx - 1);
-        const double w1 = w1_of<R>(pc), w0 = 1.0 - w1;
+        const double w1 = w1_uniform<R>(pc), w0 = w1_uniform<R>(~pc);  // mirrored within the cell: 1 - w1
+        double* Q = sQ + slot * 3 * L::NQ;
 #pragma unroll
-        for (int k = 0; k < KQ; ++k) {
-            const int i = threadIdx.x + k * NT;
-            if (i < 3 * L::NQ)
-                sQ[i] = w0 * static_cast<double>(qv0[k]) + w1 * static_cast<double>(qv1[k]);
-        }
-    };
-    auto build_q = [&](int p) {
-        load_q(p);
-        store_q(p);
+        for (int k = 0; k < L::KQ; ++k)
+            if ((k + 1) * NT <= 3 * L::NQ || t + k * NT < 3 * L::NQ)
+                Q[t + k * NT] = w0 * static_cast<double>(q0[k]) + w1 * static_cast<double>(q1[k]);
     };
 
-    // warp at in-plane position (gy, gz) (clamped into the domain) of plane p
-    // (clamped), from the x-interpolated node plane
-    auto warp_at = [&](int pc, int gy, int gz, float* dT) -> float {
-        const int jy = node_of<R>(gy), jz = node_of<R>(gz);
-        const double wy1 = w1_of<R>(gy), wz1 = w1_of<R>(gz);
-        const double wy0 = 1.0 - wy1, wz0 = 1.0 - wz1;
-        const int q = (jy - qly) * L::NQZ + (jz - qlz);
-        double yh[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double* Q = sQ + c * L::NQ + q;
-            const double c0 = wz0 * Q[0] + wz1 * Q[1];
-            const double c1 = wz0 * Q[L::NQZ] + wz1 * Q[L::NQZ + 1];
-            yh[c] = wy0 * c0 + wy1 * c1;
-        }
-        // continuous template index y_hat / h - 1/2; a power-of-two spacing has
-        // an exact reciprocal, any other is divided (correctly rounded)
+    // y_hat of a position from its four nodes of plane Q: along z, then y
+    auto lerp_z = [&](const double* Q, double w, double& lo, double& up) {
+        lo = fma(w, Q[3] - Q[0], Q[0]);
+        up = fma(w, Q[3 * L::NQZ + 3] - Q[3 * L::NQZ], Q[3 * L::NQZ]);
+    };
+    // Cell and fraction of the template index, clamped into the domain; in:
+    // inside it.  The cell is in [0, m - 2], so the fraction reaches 1 at the
+    // far end and lies outside [0, 1] exactly where the index is outside (a
+    // NaN counts as outside, with cell and fraction 0).
+    auto cell_of = [&](const double (&yh)[3], float (&f)[3], bool (&in)[3],
+                       bool slope) -> uint32_t {
+        const double hh[3] = {a.hx, a.hy, a.hz}, ih[3] = {a.ihx, a.ihy, a.ihz};
+        const int last[3] = {mx - 2, my - 2, mz - 2};
         int i0[3];
-        float f[3], s[3];
-        const double hh[3] = {a.hx, a.hy, a.hz};
-        const double ih[3] = {a.ihx, a.ihy, a.ihz};
-        const int mm[3] = {mx, my, mz};
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            const double xi = POW2 ? fma(yh[d], ih[d], -0.5) : yh[d] / hh[d] - 0.5;
-            // clamped into [0, m - 1] (a NaN goes to 0); inside the domain iff
-            // unchanged.  On [0, m - 1] the floor is the truncation, and the
-            // last cell is m - 2 (the fraction reaches 1 at the far end).
-            const double xc = fmin(fmax(xi, 0.0), static_cast<double>(mm[d] - 1));
-            s[d] = xc == xi ? 1.0f : 0.0f;
-            const int i = min(static_cast<int>(xc), mm[d] - 2);
-            i0[d] = i;
-            f[d] = static_cast<float>(xc - static_cast<double>(i));
+            const double xi = index_of<POW2>(yh[d], hh[d], ih[d]);
+            i0[d] = min(max(to_int(xi), 0), last[d]);
+            const double r = xi - static_cast<double>(i0[d]);
+            f[d] = __builtin_amdgcn_fmed3f(static_cast<float>(r), 0.0f, 1.0f);
+            settle(f[d]);
+            if (GRAD && slope) in[d] = settle_and(r >= 0.0, r <= 1.0);
         }
-        (void)pc;
-        const uint32_t tb = static_cast<uint32_t>(i0[0] * sxT + i0[1] * mz + i0[2]) * 4u;
-        const uint32_t row4 = static_cast<uint32_t>(mz) * 4u;
-        const float2 t00 = bload2(rT, tb, 0u), t01 = bload2(rT, tb, row4);
-        const float2 t10 = bload2(rT, tb, plane4), t11 = bload2(rT, tb, plane4 + row4);
-        const float v000 = t00.x, v001 = t00.y, v010 = t01.x, v011 = t01.y;
-        const float v100 = t10.x, v101 = t10.y, v110 = t11.x, v111 = t11.y;
+        return static_cast<uint32_t>((i0[0] * my + i0[1]) * mz + i0[2]) * 4u;
+    };
+    auto gather = [&](uint32_t tb, float2 (&v)[4]) {
+        v[0] = bload2(rT, tb, 0u);
+        v[1] = bload2(rT, tb, row4);
+        v[2] = bload2(rT, tb, plane4);
+        v[3] = bload2(rT, tb, plane4 + row4);
+    };
+    auto interp = [&](const float2 (&v)[4], const float (&f)[3], const bool (&in)[3],
+                      float* dT) -> float {
         const float qx = 1.0f - f[0], qy = 1.0f - f[1], qz = 1.0f - f[2];
-        const float c00 = fmaf(f[2], v001, qz * v000), c01 = fmaf(f[2], v011, qz * v010);
-        const float c10 = fmaf(f[2], v101, qz * v100), c11 = fmaf(f[2], v111, qz * v110);
+        const float c00 = fmaf(f[2], v[0].y, qz * v[0].x), c01 = fmaf(f[2], v[1].y, qz * v[1].x);
+        const float c10 = fmaf(f[2], v[2].y, qz * v[2].x), c11 = fmaf(f[2], v[3].y, qz * v[3].x);
         const float c0 = fmaf(f[1], c01, qy * c00), c1 = fmaf(f[1], c11, qy * c10);
         if (GRAD && dT != nullptr) {
             const float d0 = c01 - c00, d1 = c11 - c10;
-            const float e00 = v001 - v000, e01 = v011 - v010, e10 = v101 - v100,
-                        e11 = v111 - v110;
-            dT[0] = (c1 - c0) * (s[0] * a.fihx);
-            dT[1] = fmaf(f[0], d1, qx * d0) * (s[1] * a.fihy);
+            const float e00 = v[0].y - v[0].x, e01 = v[1].y - v[1].x;
+            const float e10 = v[2].y - v[2].x, e11 = v[3].y - v[3].x;
             const float ez0 = fmaf(f[1], e01, qy * e00), ez1 = fmaf(f[1], e11, qy * e10);
-            dT[2] = fmaf(f[0], ez1, qx * ez0) * (s[2] * a.fihz);
+            dT[0] = in[0] ? (c1 - c0) * a.fihx : 0.0f;
+            dT[1] = in[1] ? fmaf(f[0], d1, qx * d0) * a.fihy : 0.0f;
+            dT[2] = in[2] ? fmaf(f[0], ez1, qx * ez0) * a.fihz : 0.0f;
         }
         return fmaf(f[0], c1, qx * c0);
     };
 
-    // dT of the last three warped planes: dTw is written by W, dT2 (two steps
-    // old) is read by E; the registers rotate at the end of every step
-    float dTw[L::KP][3], dT1[L::KP][3], dT2[L::KP][3];
-    float acc0[L::KO], acc1[L::KO];
-#pragma unroll
-    for (int o = 0; o < L::KO; ++o) acc0[o] = acc1[o] = 0.0f;
-    int jA = jx_first;
+    // ---- rolling state, plane p of a step in slot (step mod 3) --------------
+    float tA[3] = {0, 0, 0}, tB[3] = {0, 0, 0}, tC[3] = {0, 0, 0};  // T_y at A, B, C
+    float rA[3] = {0, 0, 0}, rB[3] = {0, 0, 0}, rC[3] = {0, 0, 0};  // R at A, B, C
+    float dA[3][3] = {}, dB[3][3] = {};                             // dT_y/dy_hat at A, B
+    float xA[3] = {0, 0, 0}, xB[3] = {0, 0, 0};                     // v_x at A, B
+    float acc0[6] = {}, acc1[6] = {};  // P^T of node planes jA, jA+1: [c][lower, upper y node]
+    int jA = x0 / R, pend = -1;
     double dsum = 0.0;
-    float* part = a.part + static_cast<int64_t>(tile) * 3 * (CX / R + 1) * L::PY * L::PZ;
     const int NPc = (CX / R + 1) * L::PY * L::PZ;
+    float* part = a.part + static_cast<int64_t>(tile) * 3 * NPc;
 
-    auto flush = [&](int j, const float* acc) {
-        const int lx = j - jx_first;
-        if (lx < 0 || lx > CX / R) return;
+    // completed node plane: its z sums to LDS; one barrier later the y sums
+    // over neighbouring pairs and the store
+    auto stage = [&](const float (&acc)[6]) {
 #pragma unroll
-        for (int o = 0; o < L::KO; ++o) {
-            const int i = threadIdx.x + o * NT;
-            if (i < L::NOUT) {
-                const int c = i / (L::PY * L::PZ);
-                const int r = i - c * (L::PY * L::PZ);
-                part[c * NPc + lx * (L::PY * L::PZ) + r] = acc[o];
+        for (int i = 0; i < 6; ++i) sG[i * NT + t] = cell_sum_z<R>(acc[i], 1.0f - wz, wz);
+    };
+    auto emit = [&](int lx) {
+        // one node a thread, its three components; the last waves (the first
+        // ones have the halo)
+        int i = t - (NT - L::PY * L::PZ);
+        asm volatile("" : "+v"(i));  // its places are worked out here, not kept over the loop
+        if (i < 0) return;
+        const int ny = i / L::PZ, nz = i - ny * L::PZ;
+        // the node's cells below (their upper node) and above, along y and z
+        const bool yb = ny > 0, ya = ny < L::BY, zb = nz > 0, za = nz < L::BZ;
+        const float* gb = sG + NT + max(ny - 1, 0) * (R / 2) * TZ;
+        const float* ga = sG + min(ny, L::BY - 1) * (R / 2) * TZ;
+        const int ob = max(nz - 1, 0) * R + 1, oa = min(nz, L::BZ - 1) * R;
+        float* out = part + lx * (L::PY * L::PZ) + i;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            float v = 0.0f;
+#pragma unroll
+            for (int p = 0; p < R / 2; ++p) {
+                v += yb && zb ? gb[2 * c * NT + p * TZ + ob] : 0.0f;
+                v += yb && za ? gb[2 * c * NT + p * TZ + oa] : 0.0f;
+                v += ya && zb ? ga[2 * c * NT + p * TZ + ob] : 0.0f;
+                v += ya && za ? ga[2 * c * NT + p * TZ + oa] : 0.0f;
             }
+            out[c * NPc] = v;
         }
     };
 
-    build_q(x0 - 2);
+    {
+        float q0[L::KQ], q1[L::KQ];
+        load_q(x0 - LEAD, q0, q1);
+        store_q(x0 - LEAD, 0, q0, q1);
+    }
     __syncthreads();
 
-    auto step = [&](const int k) {
-        const int S = k % 3;  // LDS slot of the plane warped in this step
-        // ---------------- W: warp plane pw, stage R of plane pw - 1 --------
-        const int pw = x0 - 2 + k;
-        const int pwc = clampi(pw, 0, mx - 1);
-        float* Ty = sTy + S * L::NH2;
-        const bool wgrad = GRAD && pw >= x0 && pw < xend;
+    const int nstep = xend - x0 + 2 * LEAD;
+    // One step: plane pw = x0 - LEAD + k enters.  Whatever it reads from LDS
+    // was written in an earlier step.
+    auto step = [&](auto slot, const int k) {
+        constexpr int S = decltype(slot)::value;
+        constexpr int S0 = S % 3, S1 = (S + 2) % 3, S2 = (S + 1) % 3;
+        constexpr int P0 = S & 1, P1 = P0 ^ 1;  // LDS slots written in this step, in the last one
+        const int pw = x0 - LEAD + k;
+        const uint32_t pwc4 = static_cast<uint32_t>(clampi(pw, 0, mx - 1)) * plane4;
+        // halo positions this plane needs: all of them where v is formed on
+        // the halo's faces, the faces beside those planes, none at the ends
+        const bool mid = pw >= x0 && pw < xend;
+        const bool edge = GRAD && (pw == x0 - 1 || pw == xend);
+        const int nring = mid ? (GRAD ? L::NRING : L::NFACE) : (edge ? L::NFACE : 0);
+        const bool ring = t < nring;
+        // unpacked and widened where used, not kept so over the loop
+        asm volatile("" : "+v"(packC1), "+v"(packC2), "+v"(wyC), "+v"(wzC));
+        // ------------- W: P and the warp of plane pw ------------------------
+        float2 vC[4];
+        float fC[3];
+        const double* Q = sQ + P0 * 3 * L::NQ;
+        {
+            rA[S0] = bload(rR, offA, pwc4);
+            rB[S0] = bload(rR, offA, pwc4 + row4);
+            if (ring) rC[S0] = bload(rR, offC, pwc4);
+            float2 vA[4], vB[4];
+            float fA[3], fB[3];
+            bool iA[3], iB[3];
+            {
+                double yA[3], yB[3];
 #pragma unroll
-        for (int kk = 0; kk < L::KP; ++kk) {
-            const int t = threadIdx.x + kk * NT;
-            const int ly = t / TZ, lz = t % TZ;
-            const int gy = min(y0 + ly, my - 1), gz = min(z0 + lz, mz - 1);
-            Ty[(ly + 2) * L::H2Z + (lz + 2)] = warp_at(pwc, gy, gz, wgrad ? dTw[kk] : nullptr);
-        }
-        for (int s = threadIdx.x; s < L::NRING2; s += NT) {
-            int by, bz;
-            if (s < 4 * L::H2Z) {
-                const int row = s / L::H2Z;
-                by = row < 2 ? row : TY + row;
-                bz = s - row * L::H2Z;
-            } else {
-                const int q = s - 4 * L::H2Z;
-                const int col = q & 3;
-                by = 2 + (q >> 2);
-                bz = col < 2 ? col : TZ + col;
-            }
-            const int gy = clampi(y0 - 2 + by, 0, my - 1), gz = clampi(z0 - 2 + bz, 0, mz - 1);
-            Ty[by * L::H2Z + bz] = warp_at(pwc, gy, gz, nullptr);
-        }
-        const int pv = pw - 1;
-        const bool vok = pv >= max(x0 - 1, 0) && pv <= min(x0 + CX, mx - 1);
-        // prefetch for the next phases: node values of the next x-interpolated
-        // plane, and the x neighbours of R at this thread's V positions
-        if (k + 1 < nstep) load_q(pw + 1);
-        float rxm[L::KP + 1], rxp[L::KP + 1];
-        if (vok) {
-            const uint32_t sm = static_cast<uint32_t>(max(pv - 1, 0)) * plane4;
-            const uint32_t sp = static_cast<uint32_t>(min(pv + 1, mx - 1)) * plane4;
-#pragma unroll
-            for (int kk = 0; kk <= L::KP; ++kk) {
-                int b1y, b1z;
-                if (kk < L::KP) {
-                    const int t = threadIdx.x + kk * NT;
-                    b1y = t / TZ + 1;
-                    b1z = t % TZ + 1;
-                } else {
-                    ring1_pos(min(static_cast<int>(threadIdx.x), L::NRING1 - 1), b1y, b1z);
+                for (int c = 0; c < 3; ++c) {
+                    double lo, up;
+                    lerp_z(Q + qA + c, wz, lo, up);
+                    const double d = up - lo;
+                    yA[c] = fma(dwA, d, lo);
+                    yB[c] = fma(dwB, d, lo);
                 }
-                const int cy = clampi(y0 - 1 + b1y, 0, my - 1), cz = clampi(z0 - 1 + b1z, 0, mz - 1);
-                const uint32_t off = static_cast<uint32_t>(cy * mz + cz) * 4u;
-                rxm[kk] = bload(rR, off, sm);
-                rxp[kk] = bload(rR, off, sp);
+                gather(cell_of(yA, fA, iA, true), vA);
+                gather(cell_of(yB, fB, iB, true), vB);
             }
-        }
-        if (vok) {
-            const uint32_t s0 = static_cast<uint32_t>(pv) * plane4;
-            for (int i = threadIdx.x; i < L::NH2; i += NT) {
-                const int by = i / L::H2Z, bz = i - by * L::H2Z;
-                const int gy = clampi(y0 - 2 + by, 0, my - 1), gz = clampi(z0 - 2 + bz, 0, mz - 1);
-                sR[i] = bload(rR, static_cast<uint32_t>(gy * mz + gz) * 4u, s0);
-            }
-        }
-        __syncthreads();
-
-        // ---------------- V: NGF on plane pv ------------------------------
-        if (vok) {
-            const float* Tm = sTy + ((S + 1) % 3) * L::NH2;  // plane pv - 1 (slot of k - 2)
-            const float* T0 = sTy + ((S + 2) % 3) * L::NH2;  // plane pv     (slot of k - 1)
-            const float* Tp = Ty;                            // plane pv + 1 (slot of k)
-            const bool dtile = pv >= x0 && pv < xend;
-            float* Vx = sVx + (pv % 3) * L::NI;
-            float* Vy = sVy + (pv & 1) * (L::H1Y * TZ);
-            float* Vz = sVz + (pv & 1) * (TY * L::H1Z);
-            auto ngf_at = [&](int b1y, int b1z, bool inner, float rm, float rp) {
-                const int gy = y0 - 1 + b1y, gz = z0 - 1 + b1z;
-                const int cy = clampi(gy, 0, my - 1), cz = clampi(gz, 0, mz - 1);
-                const int p = (cy - y0 + 2) * L::H2Z + (cz - z0 + 2);
-                const float tau = a.tau, rho = a.rho;
-                const float gTx = (Tp[p] - Tm[p]) * a.i2hx;
-                const float gTy = (T0[p + L::H2Z] - T0[p - L::H2Z]) * a.i2hy;
-                const float gTz = (T0[p + 1] - T0[p - 1]) * a.i2hz;
-                const float gRx = (rp - rm) * a.i2hx;
-                const float gRy = (sR[p + L::H2Z] - sR[p - L::H2Z]) * a.i2hy;
-                const float gRz = (sR[p + 1] - sR[p - 1]) * a.i2hz;
-                const float aa = fmaf(gTx, gTx, fmaf(gTy, gTy, fmaf(gTz, gTz, tau * tau)));
-                const float bb = fmaf(gRx, gRx, fmaf(gRy, gRy, fmaf(gRz, gRz, rho * rho)));
-                const float ab = fmaf(gTx, gRx, fmaf(gTy, gRy, fmaf(gTz, gRz, tau * rho)));
-                const float iaa = __builtin_amdgcn_rcpf(aa), ibb = __builtin_amdgcn_rcpf(bb);
-                if (inner && dtile && gy < my && gz < mz) {
-                    // 1 - r^2 = (aa bb - ab^2) / (aa bb) with a = (grad T, tau), b = (grad R,
-                    // rho), products unfused: exactly 0 when a = b (aa = bb = ab bit for bit)
-                    float lag;
-                    {
-#pragma clang fp contract(off)
-                        lag = aa * bb - ab * ab;
-                    }
-                    dsum += static_cast<double>(lag * iaa * ibb);
-                }
-                if (GRAD) {
-                    // v = -hbar r/(nT nR) (grad R - (c/nT^2) grad T)
-                    //   = -hbar ab/(aa^2 bb) (aa grad R - ab grad T),
-                    // with unfused products so that v is exactly 0 when grad T = grad R
-                    // (then ab = aa bit for bit and both products round alike)
-                    const float coef = -a.hbar * ab * (iaa * iaa) * ibb;
-                    float wx, wy, wz;
-                    {
-#pragma clang fp contract(off)
-                        wx = aa * gRx - ab * gTx;
-                        wy = aa * gRy - ab * gTy;
-                        wz = aa * gRz - ab * gTz;
-                    }
-                    float vx = coef * wx;
-                    float vy = coef * wy;
-                    float vz = coef * wz;
-                    if (gy != cy) vy = -vy;  // mirrored ghost of the y adjoint stencil
-                    if (gz != cz) vz = -vz;
-                    const int hy = (b1y == 0 || b1y == TY + 1), hz = (b1z == 0 || b1z == TZ + 1);
-                    if (!hy && !hz) Vx[(b1y - 1) * TZ + (b1z - 1)] = vx;
-                    if (!hz) Vy[b1y * TZ + (b1z - 1)] = vy;
-                    if (!hy) Vz[(b1y - 1) * L::H1Z + b1z] = vz;
-                }
-            };
+            tA[S0] = interp(vA, fA, iA, dA[S0]);
+            tB[S0] = interp(vB, fB, iB, dB[S0]);
+            if (GRAD) {
 #pragma unroll
-            for (int kk = 0; kk < L::KP; ++kk) {
-                const int t = threadIdx.x + kk * NT;
-                ngf_at(t / TZ + 1, t % TZ + 1, true, rxm[kk], rxp[kk]);
-            }
-            if (GRAD && threadIdx.x < L::NRING1) {
-                int b1y, b1z;
-                ring1_pos(threadIdx.x, b1y, b1z);
-                ngf_at(b1y, b1z, false, rxm[L::KP], rxp[L::KP]);
-            }
-        }
-        if (!GRAD) {
-            __syncthreads();
-            if (k + 1 < nstep) store_q(pw + 1);
-            __syncthreads();
-            return;
-        }
-        __syncthreads();
-
-        // ---------------- E: adjoint on plane pe --------------------------
-        const int pe = pw - 2;
-        const bool eok = pe >= x0 && pe < xend;
-        if (eok) {
-            const float* V0 = sVx + (pe % 3) * L::NI;
-            const float* Vm = pe - 1 >= 0 ? sVx + ((pe + 2) % 3) * L::NI : nullptr;
-            const float* Vp = pe + 1 <= mx - 1 ? sVx + ((pe + 1) % 3) * L::NI : nullptr;
-            const float* Vy = sVy + (pe & 1) * (L::H1Y * TZ);
-            const float* Vz = sVz + (pe & 1) * (TY * L::H1Z);
-#pragma unroll
-            for (int kk = 0; kk < L::KP; ++kk) {
-                const int t = threadIdx.x + kk * NT;
-                const int ly = t / TZ, lz = t % TZ;
-                const float vxm = Vm ? Vm[t] : -V0[t];
-                const float vxp = Vp ? Vp[t] : -V0[t];
-                const float ex = vxm - vxp;
-                const float ey = Vy[ly * TZ + lz] - Vy[(ly + 2) * TZ + lz];
-                const float ez = Vz[ly * L::H1Z + lz] - Vz[ly * L::H1Z + lz + 2];
-                const bool in = (y0 + ly < my) && (z0 + lz < mz);
-                const float e = in ? fmaf(ex, a.i2hx, fmaf(ey, a.i2hy, ez * a.i2hz)) : 0.0f;
-                sG[t] = e * dT2[kk][0];  // dT of plane pe, warped two steps ago
-                sG[L::NI + t] = e * dT2[kk][1];
-                sG[2 * L::NI + t] = e * dT2[kk][2];
-            }
-        }
-        __syncthreads();
-
-        // ---------------- Z: P^T along z ----------------------------------
-        // node nz of the tile collects voxels R(nz-1) .. R(nz+1)-1 with the
-        // weights (2k+1)/(2R) rising then falling (the two halves of a cell)
-        const int jz0 = z0 / R, jy0 = y0 / R;
-        if (eok) {
-            for (int i = threadIdx.x; i < L::GZ; i += NT) {
-                const int nz = i % L::PZ;
-                const float* g = sG + (i / L::PZ) * TZ;  // (c, ly) row
-                float acc = 0.0f;
-#pragma unroll
-                for (int k = 0; k < R; ++k) {
-                    // voxel R(nz-1)+k: node nz is its upper node (weight w1)
-                    const int lz = R * (nz - 1) + k;
-                    if (lz >= 0) acc = fmaf((2 * k + 1) * (0.5f / R), g[lz], acc);
-                    // voxel R nz + k: node nz is its lower node (weight w0)
-                    const int lz2 = R * nz + k;
-                    if (lz2 < TZ) acc = fmaf(1.0f - (2 * k + 1) * (0.5f / R), g[lz2], acc);
-                }
-                sGz[i] = acc;
-            }
-        }
-        __syncthreads();
-
-        // ---------------- Y: P^T along y, then x into the accumulators -----
-        if (eok) {
-            const int jx = node_of<R>(pe);
-            const float wx1 = w1_of<R>(pe), wx0 = 1.0f - wx1;
-            if (jx > jA) {  // node plane jA has all its image planes: write it
-                flush(jA, acc0);
-#pragma unroll
-                for (int o = 0; o < L::KO; ++o) {
-                    acc0[o] = acc1[o];
-                    acc1[o] = 0.0f;
-                }
-                jA += 1;
-            }
-#pragma unroll
-            for (int o = 0; o < L::KO; ++o) {
-                const int i = threadIdx.x + o * NT;
-                if (i < L::NOUT) {
-                    const int nz = i % L::PZ;
-                    const int ny = (i / L::PZ) % L::PY;
-                    const int c = i / (L::PZ * L::PY);
-                    const float* gz = sGz + c * TY * L::PZ + nz;
-                    float v = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < R; ++k) {
-                        const int ly = R * (ny - 1) + k;
-                        if (ly >= 0) v = fmaf((2 * k + 1) * (0.5f / R), gz[ly * L::PZ], v);
-                        const int ly2 = R * ny + k;
-                        if (ly2 < TY) v = fmaf(1.0f - (2 * k + 1) * (0.5f / R), gz[ly2 * L::PZ], v);
-                    }
-                    acc0[o] = fmaf(wx0, v, acc0[o]);
-                    acc1[o] = fmaf(wx1, v, acc1[o]);
+                for (int c = 0; c < 3; ++c) {
+                    settle(dA[S0][c]);
+                    settle(dB[S0][c]);
                 }
             }
         }
-        if (k + 1 < nstep) store_q(pw + 1);  // sG is no longer read: Q may overwrite it
-#pragma unroll
-        for (int kk = 0; kk < L::KP; ++kk)
+        if (ring) {
+            const int qC = packC2 & 0xffffu;
+            double yC[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                dT2[kk][c] = dT1[kk][c];
-                dT1[kk][c] = dTw[kk][c];
+                double lo, up;
+                lerp_z(Q + qC + c, wzC, lo, up);
+                yC[c] = fma(static_cast<double>(wyC), up - lo, lo);
             }
+            bool iC[3];
+            gather(cell_of(yC, fC, iC, false), vC);
+        }
+        float q0[L::KQ], q1[L::KQ];  // nodes of the next plane, stored at the end of the step
+        if (k + 1 < nstep) load_q(pw + 1, q0, q1);
+        // ------------- V: NGF on plane pv = pw - 1 --------------------------
+        const int pv = pw - 1;
+        const bool vin = pv >= x0 && pv < xend;
+        const float* T0 = sTy + P1 * L::NH2;
+        const float* R0 = sR + P1 * L::NH2;
+        // NGF term at one position from its central differences (doubled)
+        auto ngf = [&](float Tx, float Ty, float Tz, float Rx, float Ry, float Rz, bool val,
+                       float& vx, float& vy, float& vz) {
+            const float gTx = Tx * a.i2hx, gTy = Ty * a.i2hy, gTz = Tz * a.i2hz;
+            const float gRx = Rx * a.i2hx, gRy = Ry * a.i2hy, gRz = Rz * a.i2hz;
+            const float aa = fmaf(gTx, gTx, fmaf(gTy, gTy, fmaf(gTz, gTz, tau2)));
+            const float bb = fmaf(gRx, gRx, fmaf(gRy, gRy, fmaf(gRz, gRz, rho2)));
+            const float ab = fmaf(gTx, gRx, fmaf(gTy, gRy, fmaf(gTz, gRz, taurho)));
+            const float iaa = __builtin_amdgcn_rcpf(aa), ibb = __builtin_amdgcn_rcpf(bb);
+            if (val) {
+                // 1 - r^2 = (aa bb - ab^2) / (aa bb) with a = (grad T, tau), b = (grad R,
+                // rho), products unfused: exactly 0 when a = b (aa = bb = ab bit for bit)
+                float lag;
+                {
+#pragma clang fp contract(off)
+                    lag = aa * bb - ab * ab;
+                }
+                const float term = lag * iaa * ibb;
+                dsum += static_cast<double>(inside ? term : 0.0f);
+            }
+            if (GRAD) {
+                // v = -hbar r/(nT nR) (grad R - (c/nT^2) grad T)
+                //   = -hbar ab/(aa^2 bb) (aa grad R - ab grad T),
+                // with unfused products so that v is exactly 0 when grad T = grad R
+                // (then ab = aa bit for bit and both products round alike)
+                const float coef = nhbar * ab * (iaa * iaa) * ibb;
+                float wx, wy, wzz;
+                {
+#pragma clang fp contract(off)
+                    wx = aa * gRx - ab * gTx;
+                    wy = aa * gRy - ab * gTy;
+                    wzz = aa * gRz - ab * gTz;
+                }
+                vx = coef * wx;
+                vy = coef * wy;
+                vz = coef * wzz;
+            }
+        };
+        if (vin || (GRAD && pv >= max(x0 - 1, 0) && pv <= min(xend, mx - 1))) {
+            const float* TA = T0 + box;
+            const float* RA = R0 + box;
+            float* Vy = sVy + P0 * L::VYS + (ly + 1) * TZ + lz;
+            float* Vz = sVz + P0 * L::VZS + ly * (TZ + 2) + lz + 1;
+            float vy, vz;
+            ngf(tA[S0] - tA[S2], tB[S1] - TA[-H2Z], TA[1] - TA[-1], rA[S0] - rA[S2],
+                rB[S1] - RA[-H2Z], RA[1] - RA[-1], vin, xA[S0], vy, vz);
+            if (GRAD && vin && (!ragged || inside)) {
+                Vy[0] = vy;
+                Vz[0] = vz;
+                if (col_end) Vz[1] = -vz;  // mirrored ghosts of the y and z adjoint stencils
+            }
+            ngf(tB[S0] - tB[S2], TA[2 * H2Z] - tA[S1], TA[H2Z + 1] - TA[H2Z - 1], rB[S0] - rB[S2],
+                RA[2 * H2Z] - rA[S1], RA[H2Z + 1] - RA[H2Z - 1], vin, xB[S0], vy, vz);
+            if (GRAD && vin) {
+                if (!ragged || inside) {
+                    Vy[TZ] = vy;
+                    Vz[TZ + 2] = vz;
+                    if (col_end) Vz[TZ + 3] = -vz;
+                    if (row_end) Vy[2 * TZ] = -vy;
+                }
+            }
+        }
+        // the halo position: its gathers were in flight over the tile's V
+        if (ring) {
+            const bool none[3] = {false, false, false};
+            tC[S0] = interp(vC, fC, none, nullptr);
+        }
+        if (GRAD && vin && face) {
+            const float* TC = T0 + (packC1 >> 16);
+            const float* RC = R0 + (packC1 >> 16);
+            float vx, vy, vz;
+            ngf(tC[S0] - tC[S2], TC[H2Z] - TC[-H2Z], TC[1] - TC[-1], rC[S0] - rC[S2],
+                RC[H2Z] - RC[-H2Z], RC[1] - RC[-1], false, vx, vy, vz);
+            const float v = yface ? vy : vz;
+            (yface ? sVy + P0 * L::VYS : sVz + P0 * L::VZS)[packC2 >> 16] = flipC ? -v : v;
+        }
+        if (GRAD) {
+            if (pend >= 0) {
+                emit(pend);
+                pend = -1;
+            }
+            // ------------- E: adjoint on plane pe = pw - 2, P^T along y and x ---
+            const int pe = pw - 2;
+            if (pe >= x0) {
+                const int jx = node_of<R>(pe);
+                const float wx1 = static_cast<float>(w1_uniform<R>(pe));
+                const float wx0 = static_cast<float>(w1_uniform<R>(~pe));
+                if (jx > jA) {  // node plane jA has all its image planes
+                    stage(acc0);
+                    pend = jA - x0 / R;
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) {
+                        acc0[i] = acc1[i];
+                        acc1[i] = 0.0f;
+                    }
+                    jA += 1;
+                }
+                const float* Vy = sVy + P1 * L::VYS + ly * TZ + lz;
+                const float* Vz = sVz + P1 * L::VZS + ly * (TZ + 2) + lz;
+                // mirrored ghosts of the x adjoint stencil at the domain's ends
+                const bool lo = pe > 0, up = pe + 1 < mx;
+                const float exA = (lo ? xA[S2] : -xA[S1]) - (up ? xA[S0] : -xA[S1]);
+                const float exB = (lo ? xB[S2] : -xB[S1]) - (up ? xB[S0] : -xB[S1]);
+                const float eyA = Vy[0] - Vy[2 * TZ], eyB = Vy[TZ] - Vy[3 * TZ];
+                const float ezA = Vz[0] - Vz[2], ezB = Vz[TZ + 2] - Vz[TZ + 4];
+                float eA = fmaf(exA, a.i2hx, fmaf(eyA, a.i2hy, ezA * a.i2hz));
+                float eB = fmaf(exB, a.i2hx, fmaf(eyB, a.i2hy, ezB * a.i2hz));
+                if (ragged) {
+                    eA = inside ? eA : 0.0f;
+                    eB = inside ? eB : 0.0f;
+                }
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const float gA = eA * dA[S2][c], gB = eB * dB[S2][c];
+                    const float gl = fmaf(1.0f - wyB, gB, (1.0f - wyA) * gA);
+                    const float gu = fmaf(wyB, gB, wyA * gA);
+                    acc0[2 * c] = fmaf(wx0, gl, acc0[2 * c]);
+                    acc0[2 * c + 1] = fmaf(wx0, gu, acc0[2 * c + 1]);
+                    acc1[2 * c] = fmaf(wx1, gl, acc1[2 * c]);
+                    acc1[2 * c + 1] = fmaf(wx1, gu, acc1[2 * c + 1]);
+                }
+            }
+        }
+        // ------------- what the next step reads -------------------------------
+        float* Tw = sTy + P0 * L::NH2 + box;
+        float* Rw = sR + P0 * L::NH2 + box;
+        if (!ragged || inside) {
+            Tw[0] = tA[S0];
+            Tw[H2Z] = tB[S0];
+            Rw[0] = rA[S0];
+            Rw[H2Z] = rB[S0];
+            if (row_end) {
+                Tw[2 * H2Z] = tB[S0];
+                Rw[2 * H2Z] = rB[S0];
+            }
+            if (col_end) {
+                Tw[1] = tA[S0];
+                Tw[H2Z + 1] = tB[S0];
+                Rw[1] = rA[S0];
+                Rw[H2Z + 1] = rB[S0];
+            }
+        }
+        if (ring) {
+            const int bc = packC1 & 0xffffu;
+            sTy[P0 * L::NH2 + bc] = tC[S0];
+            sR[P0 * L::NH2 + bc] = rC[S0];
+        }
+        if (k + 1 < nstep) store_q(pw + 1, P1, q0, q1);
         __syncthreads();
     };
-
-    for (int k = 0; k < nstep; ++k) step(k);
-    if (GRAD) {
-        flush(jA, acc0);
-        flush(jA + 1, acc1);
+    for (int k = 0; k < nstep; k += 6) {
+        step(std::integral_constant<int, 0>(), k);
+        if (k + 1 >= nstep) break;
+        step(std::integral_constant<int, 1>(), k + 1);
+        if (k + 2 >= nstep) break;
+        step(std::integral_constant<int, 2>(), k + 2);
+        if (k + 3 >= nstep) break;
+        step(std::integral_constant<int, 3>(), k + 3);
+        if (k + 4 >= nstep) break;
+        step(std::integral_constant<int, 4>(), k + 4);
+        if (k + 5 >= nstep) break;
+        step(std::integral_constant<int, 5>(), k + 5);
     }
-    const double dt = [&] {
-        double v = wave_sum(dsum);
-        const int w = threadIdx.x >> 6;
+    if (GRAD) {
+        if (pend >= 0) emit(pend);
         __syncthreads();
-        if ((threadIdx.x & 63) == 0) red[w] = v;
+        stage(acc0);
         __syncthreads();
-        if constexpr (NT == 256)
-            return (red[0] + red[1]) + (red[2] + red[3]);
-        else
-            return ((red[0] + red[1]) + (red[2] + red[3])) +
-                   ((red[4] + red[5]) + (red[6] + red[7]));
-    }();
-    if (threadIdx.x == 0) a.dpart[tile] = dt;
+        emit(jA - x0 / R);
+        __syncthreads();
+        stage(acc1);
+        __syncthreads();
+        emit(jA + 1 - x0 / R);
+    }
+    // D partial of the tile: wave sums, then the waves in order
+    const double v = wave_sum(dsum);
+    if ((t & 63) == 0) red[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) {
+        double s = (red[0] + red[1]) + (red[2] + red[3]);
+        if constexpr (NT == 512) s += (red[4] + red[5]) + (red[6] + red[7]);
+        a.dpart[tile] = s;
+    }
 }
 
-// The 16 x 32 tile needs 36 KiB of LDS, so up to four workgroups fit a CU;
-// its registers are held to four waves per SIMD (128 VGPRs, no spills).  The
-// 32 x 32 tile (512 threads, 68 KiB) fits two workgroups, also four waves
-// per SIMD.  The 16 x 64 tile is limited to two workgroups per CU by LDS.
 template <int TY, int TZ, int R, bool GRAD, bool POW2>
-__global__ __launch_bounds__((march_threads<TY, TZ>()), TZ == 32 ? 4 : 2) void k_image_march(
+__global__ __launch_bounds__((March<TY, TZ, R>::NT), 4) void k_image_march(
     ImagePassArgs a, int CX) {
     if (a.gate && *a.gate == kOpNone) return;
     march_body<TY, TZ, R, GRAD, POW2>(a, CX, blockIdx.x);
 }
 
-// each pair's chunk length is its own (a.cx).  The pair and block indices
+// Each pair's chunk length is its own (a.cx).  The pair and block indices
 // are uniform over the workgroup: taken as such, the pair's arguments load
 // into scalar registers and the kernel needs no more vector registers than
 // the single-pair one (no spills).
 template <int TY, int TZ, int R, bool POW2>
-__global__ __launch_bounds__((march_threads<TY, TZ>()), TZ == 32 ? 4 : 2) void k_image_march_batch(
+__global__ __launch_bounds__((March<TY, TZ, R>::NT), 4) void k_image_march_batch(
     const ImagePassArgs* args, const BlockRef* blk) {
     const BlockRef e = blk[blockIdx.x];
     const int pair = __builtin_amdgcn_readfirstlane(e.pair);
@@ -560,7 +676,7 @@ template <int TY, int TZ, int R>
 void launch_march_batch_t(const ImagePassArgs* args, const BlockRef* blk, int nblk, bool pow2,
                           hipStream_t s) {
     using L = March<TY, TZ, R>;
-    const size_t lds = sizeof(float) * L::LDS_FLOATS;
+    const size_t lds = sizeof(float) * L::LDS_GRAD;
     if (pow2)
         hipLaunchKernelGGL((k_image_march_batch<TY, TZ, R, true>), dim3(nblk), dim3(L::NT),
                            lds, s, args, blk);
@@ -573,7 +689,7 @@ template <int TY, int TZ, int R>
 void launch_march_t(const ImagePassArgs& a, int cx, hipStream_t s) {
     using L = March<TY, TZ, R>;
     const int blocks = a.ntx * a.nty * a.ntz;
-    const size_t lds = sizeof(float) * L::LDS_FLOATS;
+    const size_t lds = sizeof(float) * (a.want_grad ? L::LDS_GRAD : L::LDS_VALUE);
     // the spacing decides at compile time how the warp index is formed
     if (a.want_grad) {
         if (a.pow2h)
@@ -623,7 +739,7 @@ int march_per_cu() {
     using L = March<TY, TZ, 2>;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_image_march<TY, TZ, 2, true, true>,
-                                                     L::NT, sizeof(float) * L::LDS_FLOATS) !=
+                                                     L::NT, sizeof(float) * L::LDS_GRAD) !=
             hipSuccess ||
         per_cu < 1)
         per_cu = 1;

@@ -499,17 +499,24 @@ void tune_cache_store(const std::string& key, int v) {
 
 // Image-pass variant from the level size alone, for callers that cannot
 // afford timing runs (or whose timings would be disturbed by concurrent
-// work): the fastest variants measured on gfx950 at cubic levels of 256^3
-// and 128^3 (the 32 x 32 marching tile) and of 64^3 and below (the small 3D
-// tile).
+// work).  Whole evaluations on gfx950, us, 3D tile of 4 x 4 x 16 / marching
+// over 16 x 32 / over 32 x 32: 32^3 27 / 33 / 37, 64 x 80 x 48 36 / 34 / 37,
+// 64^3 38 / 36 / 39, 90 x 106 x 74 69 / 39 / 46, 96^3 75 / 41 / 42, 128^3 155 /
+// 58 / 56, 256^3 1132 / 205 / 202: a small level has too few marching
+// workgroups to fill the device, and the 32 x 32 tile has the smaller halo.
 int variant_by_size(const Level& L) {
     if (!L.dyadic) return kMarchGen;
-    return L.N() >= (int64_t{1} << 20) ? kMarchSqFit : kTile3DTiny;
+    if (L.N() >= (int64_t{1} << 20)) return kMarchSqFit;
+    return L.N() >= (int64_t{1} << 18) ? kMarch32Fit : kTile3DTiny;
 }
 
 // Pick the image-pass variant of every level: forced, cached for this shape,
 // or the fastest of all variants over three timed evaluations at the identity
-// (whole evaluation: image pass, node pass and reduction).
+// (whole evaluation: image pass, node pass and reduction).  The size rule's
+// variant is kept unless another is faster by more than kTuneMargin: several
+// come within a few per cent of each other, less than three evaluations can
+// tell apart, and two contexts should not differ by the noise of a timing.
+constexpr float kTuneMargin = 0.06f;
 ngf_status autotune(ngf_ctx* c) {
     if (c->forced_variant >= 0) {
         // a variant that needs a ratio of 2 or 4 gives way to the general
@@ -544,7 +551,8 @@ ngf_status autotune(ngf_ctx* c) {
         launch_identity(c->ltmp, L.my[0], L.my[1], L.my[2], L.hy[0], L.hy[1], L.hy[2],
                         c->stream);
         int best = L.dyadic ? kTile3D : kMarchGen;
-        float best_ms = 1e30f;
+        const int rule = variant_by_size(L);
+        float best_ms = 1e30f, rule_ms = 1e30f;
         for (int v = 0; v < kNumVariants && st == NGF_OK; ++v) {
             if (!variant_ok(L, v)) continue;
             L.variant = v;
@@ -558,11 +566,13 @@ ngf_status autotune(ngf_ctx* c) {
             if (st == NGF_OK && (hipEventSynchronize(e1) != hipSuccess ||
                                  hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
                 st = fail(c, NGF_E_HIP, "autotune timing failed");
+            if (st == NGF_OK && v == rule) rule_ms = ms;
             if (st == NGF_OK && ms < best_ms) {
                 best_ms = ms;
                 best = v;
             }
         }
+        if (rule_ms < 1e30f && best_ms > (1.0f - kTuneMargin) * rule_ms) best = rule;
         L.variant = best;
         c->tune_cache.emplace_back(key, best);
         tune_cache_store(key, best);
