@@ -181,7 +181,7 @@ ngf_status ngf_build_pyramid(ngf_ctx* ctx, const float* R, const float* T,
 ngf_status ngf_set_node_grid(ngf_ctx* ctx, const int32_t my0[3]);
 
 /* Image-grid kernel of the evaluation.  `variant`: -2 = by level size (no
- * timing runs: at least 1 Mi voxels -> 13, at least 256 Ki -> 11, else 8);
+ * timing runs: at least 1 Mi voxels -> 13, at least 384 Ki -> 11, else 8);
  * -1 = autotune (default:
  * at ngf_build_pyramid every level times each variant over three evaluations
  * at the identity and keeps the fastest, or the size rule's where that is

@@ -705,9 +705,7 @@ void launch_image_tile_atomic(const ImagePassArgs& a, hipStream_t s) {
 
 template <int RATIO>
 void launch_image_ratio_atomic(const ImagePassArgs& a, int variant, hipStream_t s) {
-    if (variant == kTile3DTiny)
-        launch_image_tile_atomic<4, 4, 16, RATIO>(a, s);
-    else if (variant == kTile3DSmall)
+    if (variant == kTile3DSmall)
         launch_image_tile_atomic<4, 8, 32, RATIO>(a, s);
     else
         launch_image_tile_atomic<kTX, kTY, kTZ, RATIO>(a, s);
@@ -731,8 +729,6 @@ void launch_image_ratio_batch(const ImagePassArgs* args, const BlockRef* blk, in
                               int variant, bool pow2, hipStream_t s) {
     if (variant == kTile3DSmall)
         launch_image_tile_batch<4, 8, 32, RATIO>(args, blk, nblk, pow2, s);
-    else if (variant == kTile3DTiny)
-        launch_image_tile_batch<4, 4, 16, RATIO>(args, blk, nblk, pow2, s);
     else
         launch_image_tile_batch<kTX, kTY, kTZ, RATIO>(args, blk, nblk, pow2, s);
 }
@@ -741,17 +737,17 @@ template <int RATIO>
 void launch_image_ratio(const ImagePassArgs& a, int variant, hipStream_t s) {
     if (variant == kTile3DSmall)
         launch_image_tile<4, 8, 32, RATIO>(a, s);
-    else if (variant == kTile3DTiny)
-        launch_image_tile<4, 4, 16, RATIO>(a, s);
     else
         launch_image_tile<kTX, kTY, kTZ, RATIO>(a, s);
 }
 
 }  // namespace
 
-// 3D-tile variants (kTile3D, kTile3DSmall, kTile3DTiny)
+// 3D-tile variants (kTile3D, kTile3DSmall; kTile3DTiny has a kernel of its own)
 void launch_image_pass(const ImagePassArgs& a, int ratio, int variant, hipStream_t s) {
-    if (ratio == 2)
+    if (variant == kTile3DTiny)
+        launch_image_cube(a, ratio, s);
+    else if (ratio == 2)
         launch_image_ratio<2>(a, variant, s);
     else if (ratio == 4)
         launch_image_ratio<4>(a, variant, s);
@@ -761,7 +757,9 @@ void launch_image_pass(const ImagePassArgs& a, int ratio, int variant, hipStream
 void launch_image_pass_batch(const ImagePassArgs* args, const BlockRef* blk, int nblk, int ratio,
                              int variant, bool pow2, hipStream_t s) {
     if (nblk <= 0) return;
-    if (ratio == 2)
+    if (variant == kTile3DTiny)
+        launch_image_cube_batch(args, blk, nblk, ratio, pow2, s);
+    else if (ratio == 2)
         launch_image_ratio_batch<2>(args, blk, nblk, variant, pow2, s);
     else if (ratio == 4)
         launch_image_ratio_batch<4>(args, blk, nblk, variant, pow2, s);

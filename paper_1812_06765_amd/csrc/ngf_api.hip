@@ -500,14 +500,15 @@ void tune_cache_store(const std::string& key, int v) {
 // Image-pass variant from the level size alone, for callers that cannot
 // afford timing runs (or whose timings would be disturbed by concurrent
 // work).  Whole evaluations on gfx950, us, 3D tile of 4 x 4 x 16 / marching
-// over 16 x 32 / over 32 x 32: 32^3 27 / 33 / 37, 64 x 80 x 48 36 / 34 / 37,
-// 64^3 38 / 36 / 39, 90 x 106 x 74 69 / 39 / 46, 96^3 75 / 41 / 42, 128^3 155 /
-// 58 / 56, 256^3 1132 / 205 / 202: a small level has too few marching
-// workgroups to fill the device, and the 32 x 32 tile has the smaller halo.
+// over 16 x 32 / over 32 x 32: 32^3 21 / 34 / 37, 64 x 80 x 48 29 / 35 / 37,
+// 64^3 31 / 36 / 39, 90 x 106 x 74 58 / 40 / 46, 96^3 65 / 42 / 42, 128^3 130 /
+// 58 / 57, 256^3 892 / 208 / 204: a small level has too few marching
+// workgroups to fill the device and is bound by their chain of planes, a
+// large one by the halo's work.
 int variant_by_size(const Level& L) {
     if (!L.dyadic) return kMarchGen;
     if (L.N() >= (int64_t{1} << 20)) return kMarchSqFit;
-    return L.N() >= (int64_t{1} << 18) ? kMarch32Fit : kTile3DTiny;
+    return L.N() >= 3 * (int64_t{1} << 17) ? kMarch32Fit : kTile3DTiny;
 }
 
 // Pick the image-pass variant of every level: forced, cached for this shape,

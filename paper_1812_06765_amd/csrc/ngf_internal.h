@@ -337,6 +337,9 @@ void launch_identity(float* y, int nx, int ny, int nz, double hx, double hy, dou
                      hipStream_t s);
 void launch_prolongate(const float* yc, float* yf, int cx, int cy, int cz, hipStream_t s);
 void launch_image_pass(const ImagePassArgs& a, int ratio, int variant, hipStream_t s);
+void launch_image_cube(const ImagePassArgs& a, int ratio, hipStream_t s);
+void launch_image_cube_batch(const ImagePassArgs* args, const BlockRef* blk, int nblk, int ratio,
+                             bool pow2, hipStream_t s);
 void launch_image_march(const ImagePassArgs& a, int ratio, int ty, int tz, int cx,
                         hipStream_t s);
 void launch_image_gen(const ImagePassArgs& a, int cx, hipStream_t s);

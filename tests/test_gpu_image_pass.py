@@ -19,7 +19,7 @@ def _t(a):
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
 
 
-MARCH = ("march32x8", "march32fit", "march64fit", "march32sq")
+KERNELS = ("march32x8", "march32fit", "march64fit", "march32sq", "tile3d_tiny")
 
 # (m, h, ratio): below, at and just past the tiles' 16, 32 and 64 rows and
 # columns, chunks cut to one node cell, spacings with and without an exact
@@ -38,7 +38,7 @@ EDGES = [
 
 @pytest.mark.parametrize("m,h,ratio", EDGES)
 @pytest.mark.parametrize("amp", [0.4, 30.0])
-def test_march_edges(gpu_lib, m, h, ratio, amp):
+def test_edges(gpu_lib, m, h, ratio, amp):
     """amp 30: many points outside the domain."""
     ngf = gpu_lib
     rng = np.random.default_rng(17)
@@ -51,7 +51,7 @@ def test_march_edges(gpu_lib, m, h, ratio, amp):
     with ngf.Context(alpha=0.1, tau=10.0, rho=10.0, levels=1, ratio=ratio) as ctx:
         ctx.set_kernel("by_size")
         ctx.build_pyramid(_t(R), _t(T), h)
-        for v in MARCH:
+        for v in KERNELS:
             print(f"[edges] m={m} h={h} ratio={ratio} amp={amp} kernel={v}", flush=True)
             sys.stdout.flush()
             ctx.set_kernel(v)
@@ -63,7 +63,8 @@ def test_march_edges(gpu_lib, m, h, ratio, amp):
             assert abs(Jv - J) <= 1e-12 * abs(J), v
 
 
-def test_march_infinite_and_nan_positions(gpu_lib):
+@pytest.mark.parametrize("variant", ["march32sq", "tile3d_tiny"])
+def test_infinite_and_nan_positions(gpu_lib, variant):
     """A non-finite deformation is reported, whatever the kernel makes of it."""
     ngf = gpu_lib
     m = (16, 32, 32)
@@ -71,7 +72,7 @@ def test_march_infinite_and_nan_positions(gpu_lib):
     img = _t(rng.standard_normal(m))
     for h in ((1.0, 1.0, 1.0), (0.9, 0.9, 0.9)):
         with ngf.Context(alpha=0.1, tau=1.0, rho=1.0, levels=1) as ctx:
-            ctx.set_kernel("march32sq")
+            ctx.set_kernel(variant)
             ctx.build_pyramid(img, img, h)
             for bad in (float("nan"), float("inf"), float("-inf")):
                 y = ctx.identity(0)
