@@ -15,14 +15,10 @@
 //     - P^T restricted to the tile: separable weighted sums (z, y, x) onto the
 //       (B+1)^3 nodes the tile touches, written as one partial block per tile.
 //   Every write has one owner, so nothing races and nothing is atomic.
-// * node pass (one workgroup per node tile): gathers the (at most 8) tile
-//   partials of each node (this completes the sum of Eq. 3), adds
-//   alpha grad S with grad S = hbar^y A(A(y - X)) from LDS halo tiles, and
-//   writes grad J once.
+// * node pass (k_node.hip): completes the sum of Eq. 3 from the tile partials
+//   and adds alpha grad S.
 // * reduce: fixed-order float64 sums of the block partials of D and S.
 #include "ngf_internal.h"
-
-#include <atomic>
 
 #include <math.h>
 
@@ -36,10 +32,6 @@ __device__ inline double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
     return v;
 }
-__device__ inline double wave_max(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_down(v, o, 64));
-    return v;
-}
 
 // Sum over the workgroup (four wave64s) in a fixed order; result in thread 0.
 __device__ inline double block_sum(double v, double* sh) {
@@ -50,16 +42,6 @@ __device__ inline double block_sum(double v, double* sh) {
     __syncthreads();
     double r = 0.0;
     if (threadIdx.x == 0) r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-    return r;
-}
-__device__ inline double block_max(double v, double* sh) {
-    v = wave_max(v);
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[w] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0) r = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
     return r;
 }
 
@@ -423,239 +405,10 @@ __device__ __forceinline__ void image_body(const ImagePassArgs& a, int block) {
     }
 }
 
-// ------------------------------------------------------------------------
-// node pass
-// ------------------------------------------------------------------------
 template <int TX, int TY, int TZ, int RATIO, bool GRAD, bool ATOMIC, bool POW2>
 __global__ __launch_bounds__(kThreads) void k_image_pass(ImagePassArgs a) {
     if (a.gate && *a.gate == kOpNone) return;
     image_body<TX, TY, TZ, RATIO, GRAD, ATOMIC, POW2>(a, blockIdx.x);
-}
-
-// Node pass, marching form: one workgroup per (component, NY x NZ node tile
-// in (y, z), chunk of a.cxn node planes along x); thread t owns the in-plane node
-// (t / NZ, t % NZ) of every plane of the chunk.  u = y - X is kept in three
-// rolling LDS planes with a two-node in-plane halo, A u in three rolling
-// planes with a one-node halo.  Ghost nodes replicate the boundary node
-// (for u and for A u): in-plane through clamped loads and zero offsets, across
-// planes by reading the boundary plane's slot.  Step k loads u of plane
-// x0 - 2 + k, forms A u of plane x0 - 3 + k and A(A u) of plane x0 - 4 + k.
-//
-// The loop is kept free of per-lane branches and of per-plane index
-// arithmetic on the scalar unit: the LDS planes are padded to whole passes of
-// the workgroup (the surplus lanes work on a clamped copy and write into the
-// padding), the plane slots rotate, the plane offsets advance by one plane
-// per step, and lanes outside the grid compute on clamped data and store
-// nothing.  GRAD: the gradient is wanted; GATHER: it collects the image-tile
-// partials (else grad holds grad D on entry).
-template <int NY, int NZ, bool GRAD, bool GATHER>
-__device__ __forceinline__ void node_march_body(const NodePassArgs& a, int block) {
-    static_assert(NY * NZ == kThreads, "one node per thread and plane");
-    constexpr int UY = NY + 4, UZ = NZ + 4, NU = UY * UZ;  // u plane, halo 2
-    constexpr int AY = NY + 2, AZ = NZ + 2, NA = AY * AZ;  // A u plane, halo 1
-    constexpr int KU = (NU + kThreads - 1) / kThreads, KA = (NA + kThreads - 1) / kThreads;
-    constexpr int SU = KU * kThreads, SA = KA * kThreads;  // padded plane sizes
-    __shared__ float su[3 * SU];
-    __shared__ float sAu[3 * SA];
-    __shared__ double red[4];
-
-    const int ntile = a.nbx * a.nby * a.nbz;
-    const int bid = xcd_tile(block, 3 * ntile);
-    const int c = bid / ntile;
-    const int blk = bid - c * ntile;
-    const int bz = blk % a.nbz;
-    const int byy = (blk / a.nbz) % a.nby;
-    const int bx = blk / (a.nbz * a.nby);
-    const int x0 = bx * a.cxn, y0 = byy * NY, z0 = bz * NZ;
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int nn = nx * ny * nz;
-    const int plane = ny * nz;
-    const int xend = min(x0 + a.cxn, nx);
-    const int nstep = xend - x0 + 4;  // a chunk cut short by the grid stops after its last plane
-    const int PX = a.px, PY = a.py, PZ = a.pz;
-    const int NP = PX * PY * PZ;
-    const float sc = (!GATHER && a.gscale != nullptr) ? static_cast<float>(*a.gscale) : 1.0f;
-    const double hyc = c == 0 ? a.hyx : (c == 1 ? a.hyy : a.hyz);
-
-    // this thread's node (y, z) and its fixed in-plane data
-    const int ly = threadIdx.x / NZ, lz = threadIdx.x % NZ;
-    const int gy = y0 + ly, gz = z0 + lz;
-    const bool own = gy < ny && gz < nz;
-    const int q = (ly + 1) * AZ + (lz + 1);
-    const int dyp = gy + 1 < ny ? AZ : 0, dym = gy > 0 ? AZ : 0;
-    const int dzp = gz + 1 < nz ? 1 : 0, dzm = gz > 0 ? 1 : 0;
-    const int gofs = min(gy, ny - 1) * nz + min(gz, nz - 1);  // in-plane offset (clamped)
-    // u halo entries of this thread (the padding lanes repeat the last one):
-    // clamped in-plane offset and the coordinate X is taken along
-    int uoff[KU];
-    float ugc[KU];
-#pragma unroll
-    for (int k = 0; k < KU; ++k) {
-        const int i = min(static_cast<int>(threadIdx.x) + k * kThreads, NU - 1);
-        const int iy = i / UZ, iz = i - (i / UZ) * UZ;
-        const int cy = clampi(y0 - 2 + iy, 0, ny - 1), cz = clampi(z0 - 2 + iz, 0, nz - 1);
-        uoff[k] = cy * nz + cz;
-        ugc[k] = static_cast<float>(c == 1 ? cy : cz);
-    }
-    // A u halo entries of this thread: their (clamped) node's place in the u plane
-    int apos[KA];
-#pragma unroll
-    for (int k = 0; k < KA; ++k) {
-        const int i = min(static_cast<int>(threadIdx.x) + k * kThreads, NA - 1);
-        const int iy = i / AZ, iz = i - (i / AZ) * AZ;
-        const int cy = clampi(y0 - 1 + iy, 0, ny - 1), cz = clampi(z0 - 1 + iz, 0, nz - 1);
-        apos[k] = (cy - y0 + 2) * UZ + (cz - z0 + 2);
-    }
-    // gather of the image-tile partials (Eq. 3 completed): a node lies in the
-    // blocks of at most two image tiles per axis, those of the first and the
-    // last image point of its index set.  The (y, z) part of the node's place
-    // in each (j = 2 oy + oz: second tile along y if oy, along z if oz) is
-    // fixed over the chunk; the x part is the same for the whole workgroup
-    // and is tabulated per plane of the chunk.  An entry that does not apply
-    // reads offset 0 of the tile row and is not added.  The part array of one
-    // x-slab of tiles is below 2^31 floats (checked by the host).
-    int yzoff[4] = {0, 0, 0, 0};
-    bool yzok[4] = {false, false, false, false};
-    if constexpr (GATHER) {
-        const NodeTiles ty = node_tiles(min(gy, ny - 1), a.my, ny, a.tey);
-        const NodeTiles tz = node_tiles(min(gz, nz - 1), a.mz, nz, a.tez);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int oy = j >> 1, oz = j & 1;
-            const int tty = oy ? ty.tb : ty.ta, ttz = oz ? tz.tb : tz.ta;
-            const int lyy = oy ? ty.lb : ty.la, lzz = oz ? tz.lb : tz.la;
-            yzok[j] = own && tty >= 0 && ttz >= 0;
-            yzoff[j] = yzok[j] ? ((tty * a.ntz + ttz) * 3 + c) * NP + lyy * PZ + lzz : 0;
-        }
-    }
-    const int64_t xslab = static_cast<int64_t>(a.nty) * a.ntz * 3 * NP;
-    __shared__ int4 sxt[GATHER ? kNodeChunkMax : 1];
-    for (int i = threadIdx.x; GATHER && i < xend - x0; i += kThreads) {
-        const NodeTiles tx = node_tiles(x0 + i, a.mx, nx, a.tex);
-        sxt[i] = make_int4(tx.ta, tx.la, tx.tb, tx.lb);
-    }
-
-    // y of this thread's entries of the u plane, loaded one step ahead so
-    // that the loads overlap the previous plane's A u and output phases
-    int64_t ycur = static_cast<int64_t>(c) * nn + static_cast<int64_t>(x0 - 2) * plane;
-    float upre[KU];
-    auto load_u = [&](int pu, int64_t yo) {
-        if (pu < 0 || pu >= nx) return;  // planes outside the grid are never read
-        const float* yp = a.y + yo;
-#pragma unroll
-        for (int kk = 0; kk < KU; ++kk) upre[kk] = yp[uoff[kk]];
-    };
-    load_u(x0 - 2, ycur);
-    // this thread's output element: component c, plane po, in-plane offset
-    int64_t grow = static_cast<int64_t>(c) * nn + static_cast<int64_t>(x0) * plane + gofs;
-    // slots of the three rolling planes: s0 = k mod 3, s1 = (k + 1) mod 3, s2 = (k + 2) mod 3
-    int s0 = 0, s1 = 1, s2 = 2;
-    double ssum = 0.0, gmax = 0.0, g2 = 0.0;
-    for (int k = 0; k < nstep; ++k) {
-        // u of plane pu
-        const int pu = x0 - 2 + k;
-        if (pu >= 0 && pu < nx) {
-            float* U = su + s0 * SU;
-            const double gx = static_cast<double>(pu);
-#pragma unroll
-            for (int kk = 0; kk < KU; ++kk) {
-                const double gcd = c == 0 ? gx : static_cast<double>(ugc[kk]);
-                U[threadIdx.x + kk * kThreads] =
-                    static_cast<float>(static_cast<double>(upre[kk]) - gcd * hyc);
-            }
-        }
-        ycur += plane;
-        if (k + 1 < nstep) load_u(pu + 1, ycur);
-        __syncthreads();
-        // A u of plane pa, from u planes pa - 1, pa, pa + 1 (replicated ghosts)
-        const int pa = pu - 1;
-        if (pa >= 0 && pa < nx) {
-            const float* U0 = su + s2 * SU;                        // plane pa
-            const float* Um = pa > 0 ? su + s1 * SU : U0;          // plane pa - 1
-            const float* Up = pa + 1 < nx ? su + s0 * SU : U0;     // plane pa + 1
-            float* A = sAu + s0 * SA;
-#pragma unroll
-            for (int kk = 0; kk < KA; ++kk) {
-                const int p = apos[kk];
-                const float u0 = U0[p];
-                const float lx = Up[p] - 2.0f * u0 + Um[p];
-                const float lyv = U0[p + UZ] - 2.0f * u0 + U0[p - UZ];
-                const float lzv = U0[p + 1] - 2.0f * u0 + U0[p - 1];
-                A[threadIdx.x + kk * kThreads] = fmaf(lx, a.ihy2x, fmaf(lyv, a.ihy2y, lzv * a.ihy2z));
-            }
-        }
-        __syncthreads();
-        // A(A u) and the gradient at plane po
-        const int po = pu - 2;
-        if (po >= x0 && po < xend) {
-            const float* A0 = sAu + s2 * SA;                       // plane po
-            const float* Am = po > 0 ? sAu + s1 * SA : A0;         // plane po - 1
-            const float* Ap = po + 1 < nx ? sAu + s0 * SA : A0;    // plane po + 1
-            const float au = A0[q];
-            ssum += own ? static_cast<double>(au) * static_cast<double>(au) : 0.0;
-            if (GRAD) {
-                float gd = 0.0f;
-                if (!GATHER) {
-                    gd = a.grad[grow];
-                } else {
-                    // Eq. 3 completed: the (at most 8) image-tile partials of the
-                    // node, in the order (ox, oy, oz)
-                    const int4 xt = sxt[po - x0];
-#pragma unroll
-                    for (int ox = 0; ox < 2; ++ox) {
-                        const int ttx = ox ? xt.z : xt.x;
-                        if (ttx < 0) continue;
-                        const float* px = a.part + ttx * xslab + (ox ? xt.w : xt.y) * (PY * PZ);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const float v = px[yzoff[j]];
-                            gd = yzok[j] ? gd + v : gd;
-                        }
-                    }
-                }
-                const float lxx = Ap[q] - 2.0f * au + Am[q];
-                const float lyy = A0[q + dyp] - 2.0f * au + A0[q - dym];
-                const float lzz = A0[q + dzp] - 2.0f * au + A0[q - dzm];
-                const float aau = fmaf(lxx, a.ihy2x, fmaf(lyy, a.ihy2y, lzz * a.ihy2z));
-                const float g = fmaf(a.alpha_hbary * sc, aau, gd);
-                if (own) a.grad[grow] = g;
-                gmax = own ? fmax(gmax, static_cast<double>(fabsf(g))) : gmax;
-                g2 += own ? static_cast<double>(g) * static_cast<double>(g) : 0.0;
-                grow += plane;
-            }
-        }
-        const int t = s0;
-        s0 = s1;
-        s1 = s2;
-        s2 = t;
-    }
-    const double st = block_sum(ssum, red);
-    if (threadIdx.x == 0) a.spart[bid] = st;
-    if (GRAD) {
-        const double gm = block_max(gmax, red);
-        const double gq = block_sum(g2, red);
-        if (threadIdx.x == 0) {
-            a.gpart[2 * bid] = gm;
-            a.gpart[2 * bid + 1] = gq;
-        }
-    }
-}
-
-// GRAD: the gradient is wanted; GATHER: it collects the image-tile partials
-template <bool GRAD, bool GATHER>
-__global__ __launch_bounds__(kThreads) void k_node_pass(NodePassArgs a) {
-    if (a.gate && *a.gate == kOpNone) return;
-    node_march_body<kNMY, kNMZ, GRAD, GATHER>(a, blockIdx.x);
-}
-
-// the batched rounds always want the gradient gathered from the image pass
-__global__ __launch_bounds__(kThreads) void k_node_pass_batch(const NodePassArgs* args,
-                                                              const BlockRef* blk) {
-    const BlockRef e = blk[blockIdx.x];
-    if (e.pair < 0) return;
-    const NodePassArgs& a = args[e.pair];
-    if (a.gate && *a.gate == kOpNone) return;
-    node_march_body<kNMY, kNMZ, true, true>(a, e.block);
 }
 
 template <int TX, int TY, int TZ, int RATIO, bool POW2>
@@ -765,49 +518,11 @@ void launch_image_pass_batch(const ImagePassArgs* args, const BlockRef* blk, int
         launch_image_ratio_batch<4>(args, blk, nblk, variant, pow2, s);
 }
 
-void launch_node_pass_batch(const NodePassArgs* args, const BlockRef* blk, int nblk,
-                            hipStream_t s) {
-    if (nblk <= 0) return;
-    hipLaunchKernelGGL(k_node_pass_batch, dim3(nblk), dim3(kThreads), 0, s, args, blk);
-}
-
 void launch_image_pass_atomic(const ImagePassArgs& a, int ratio, int variant, hipStream_t s) {
     if (ratio == 2)
         launch_image_ratio_atomic<2>(a, variant, s);
     else if (ratio == 4)
         launch_image_ratio_atomic<4>(a, variant, s);
-}
-
-int node_march_slots() {
-    static std::atomic<int> cache[16];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0) dev = 0;
-    std::atomic<int>& slot = cache[dev & 15];
-    int v = slot.load();
-    if (v > 0) return v;
-    int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_node_pass<true, true>, kThreads,
-                                                     0) !=
-            hipSuccess ||
-        per_cu < 1)
-        per_cu = 8;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1)
-        cus = 256;
-    (void)hipGetLastError();
-    v = per_cu * cus;
-    slot.store(v);
-    return v;
-}
-
-void launch_node_pass(const NodePassArgs& a, hipStream_t s) {
-    const int blocks = 3 * a.nbx * a.nby * a.nbz;
-    if (!a.want_grad)
-        hipLaunchKernelGGL((k_node_pass<false, false>), dim3(blocks), dim3(kThreads), 0, s, a);
-    else if (a.gather)
-        hipLaunchKernelGGL((k_node_pass<true, true>), dim3(blocks), dim3(kThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_node_pass<true, false>), dim3(blocks), dim3(kThreads), 0, s, a);
 }
 
 }  // namespace ngf

@@ -149,22 +149,25 @@ bool pow2(double h) {
     int e = 0;
     return std::frexp(h, &e) == 0.5;
 }
-// node-pass x chunk (node planes), fitted like the image pass's
+// node-pass x chunk of the marching form (node planes), fitted like the image pass's
 int node_chunk(const Level& L) {
-    return fit_chunk(L.my[0], 3 * int64_t{tiles(L.my[1], kNMY)} * tiles(L.my[2], kNMZ), 1, 4,
+    const NodeForm& f = kNodeForm[2];
+    return fit_chunk(L.my[0], int64_t{tiles(L.my[1], f.y)} * tiles(L.my[2], f.z), 1, 4,
                      node_march_slots(), kNodeChunkMax);
 }
-// node-pass workgroups per axis (one per node tile and component)
-void node_grid(const Level& L, int nb[3]) {
-    nb[0] = tiles(L.my[0], node_chunk(L));
-    nb[1] = tiles(L.my[1], kNMY);
-    nb[2] = tiles(L.my[2], kNMZ);
+// node-pass workgroups per axis (one per node tile) of a form
+void node_grid(const Level& L, int form, int nb[3]) {
+    const NodeForm& f = kNodeForm[form];
+    nb[0] = tiles(L.my[0], f.x > 0 ? f.x : node_chunk(L));
+    nb[1] = tiles(L.my[1], f.y);
+    nb[2] = tiles(L.my[2], f.z);
 }
-int64_t node_blocks(const Level& L) {
+int64_t node_blocks_of(const Level& L, int form) {
     int nb[3];
-    node_grid(L, nb);
-    return 3 * static_cast<int64_t>(nb[0]) * nb[1] * nb[2];
+    node_grid(L, form, nb);
+    return static_cast<int64_t>(nb[0]) * nb[1] * nb[2];
 }
+int64_t node_blocks(const Level& L) { return node_blocks_of(L, node_form_of(L.Ny())); }
 
 ngf_status ensure_scratch(ngf_ctx* c, const Level& L) {
     size_t pf = 0, nt = 0;
@@ -178,7 +181,8 @@ ngf_status ensure_scratch(ngf_ctx* c, const Level& L) {
         if (slab >= (int64_t{1} << 31))
             return fail(c, NGF_E_SHAPE, "image too large in y and z for the tile layout");
     }
-    const size_t nb = static_cast<size_t>(node_blocks(L));
+    // the coarser levels may take another node-pass form
+    const size_t nb = static_cast<size_t>(std::max({node_blocks_of(L, 0), node_blocks_of(L, 1), node_blocks_of(L, 2)}));
     if (pf > c->part_cap || nt > c->dpart_cap || nb > c->nblk_cap)
         HIPCHK(c, hipStreamSynchronize(c->stream));  // queued work may use the old buffers
     if (pf > c->part_cap) {
@@ -373,11 +377,12 @@ EvalArgs eval_args(ngf_ctx* c, const Level& L, const float* R, const float* T, c
     b.py = g.py;
     b.pz = g.pz;
     int nb[3];
-    node_grid(L, nb);
+    b.form = node_form_of(L.Ny());
+    b.cxn = node_chunk(L);
+    node_grid(L, b.form, nb);
     b.nbx = nb[0];
     b.nby = nb[1];
     b.nbz = nb[2];
-    b.cxn = node_chunk(L);
     b.hyx = L.hy[0];
     b.hyy = L.hy[1];
     b.hyz = L.hy[2];
@@ -732,11 +737,12 @@ ngf_status eval_scatter(ngf_ctx* c, const Level& P, const float* R, const float*
     b.ny = P.my[1];
     b.nz = P.my[2];
     int nb[3];
-    node_grid(P, nb);
+    b.form = node_form_of(P.Ny());
+    b.cxn = node_chunk(P);
+    node_grid(P, b.form, nb);
     b.nbx = nb[0];
     b.nby = nb[1];
     b.nbz = nb[2];
-    b.cxn = node_chunk(P);
     b.hyx = P.hy[0];
     b.hyy = P.hy[1];
     b.hyz = P.hy[2];

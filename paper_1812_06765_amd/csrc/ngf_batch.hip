@@ -100,7 +100,7 @@ struct LevelTables {
         size_t off = 0;
     };
     std::vector<Group> groups;
-    std::vector<BlockRef> node_blk, vec_blk;
+    std::vector<BlockRef> node_blk[kNodeForms], vec_blk;  // node blocks by node-pass form
 };
 
 template <class T>
@@ -252,7 +252,7 @@ ngf_status graph_register(ngf_batch* b, int np, const float* const* R, const flo
             t.vec.push_back(v);
             // block tables
             add_blocks(group_of(t, lv).blk, i, geometry(lv, lv.variant).ntiles());
-            add_blocks(t.node_blk, i, node_blocks(lv));
+            add_blocks(t.node_blk[node_form_of(lv.Ny())], i, node_blocks(lv));
             add_blocks(t.vec_blk, i, v.nblocks);
         }
         // upload the tables (one device buffer, grown outside the rounds)
@@ -262,7 +262,8 @@ ngf_status graph_register(ngf_batch* b, int np, const float* const* R, const flo
         const size_t o_red0 = put(host, t.red0), o_red1 = put(host, t.red1);
         const size_t o_vec = put(host, t.vec);
         for (auto& g : t.groups) g.off = put(host, g.blk);
-        const size_t o_nblk = put(host, t.node_blk);
+        size_t o_nblk[kNodeForms];
+        for (int f = 0; f < kNodeForms; ++f) o_nblk[f] = put(host, t.node_blk[f]);
         const size_t o_vblk = put(host, t.vec_blk);
         const size_t o_ctl = align_up(host.size(), 256);
         host.resize(o_ctl + np * sizeof(LbCtl));
@@ -276,9 +277,10 @@ ngf_status graph_register(ngf_batch* b, int np, const float* const* R, const flo
         const auto* vec = static_cast<const LbVecArgs*>(P(o_vec));
         const int nvb = static_cast<int>(t.vec_blk.size());
         auto node_stage = [&](size_t o_args) {
-            launch_node_pass_batch(static_cast<const NodePassArgs*>(P(o_args)),
-                                   static_cast<const BlockRef*>(P(o_nblk)),
-                                   static_cast<int>(t.node_blk.size()), s);
+            for (int f = 0; f < kNodeForms; ++f)
+                launch_node_pass_batch(static_cast<const NodePassArgs*>(P(o_args)),
+                                       static_cast<const BlockRef*>(P(o_nblk[f])),
+                                       static_cast<int>(t.node_blk[f].size()), f, s);
         };
         // level start: evaluation at the start point, state reset
         image_stage(o_img0);
@@ -388,18 +390,20 @@ ngf_status batch_eval(ngf_batch* b, int lev, const float* const* y, double* J,
         t.node0.push_back(e.b);
         red.push_back(e.r);
         add_blocks(group_of(t, lv).blk, i, geometry(lv, lv.variant).ntiles());
-        add_blocks(t.node_blk, i, node_blocks(lv));
+        add_blocks(t.node_blk[node_form_of(lv.Ny())], i, node_blocks(lv));
     }
     std::vector<char> host;
     const size_t o_img = put(host, t.img0), o_node = put(host, t.node0), o_red = put(host, red);
     for (auto& g : t.groups) g.off = put(host, g.blk);
-    const size_t o_nblk = put(host, t.node_blk);
+    size_t o_nblk[kNodeForms];
+    for (int f = 0; f < kNodeForms; ++f) o_nblk[f] = put(host, t.node_blk[f]);
     if (const ngf_status us = upload_tables(b, host, host.size()); us != NGF_OK) return us;
     const char* d = b->dtab;
     launch_image_groups(t.groups, d, o_img, b->p.ratio, s);
-    launch_node_pass_batch(reinterpret_cast<const NodePassArgs*>(d + o_node),
-                           reinterpret_cast<const BlockRef*>(d + o_nblk),
-                           static_cast<int>(t.node_blk.size()), s);
+    for (int f = 0; f < kNodeForms; ++f)
+        launch_node_pass_batch(reinterpret_cast<const NodePassArgs*>(d + o_node),
+                               reinterpret_cast<const BlockRef*>(d + o_nblk[f]),
+                               static_cast<int>(t.node_blk[f].size()), f, s);
     launch_reduce_batch(reinterpret_cast<const ReduceArgs*>(d + o_red), np, s);
     if (hipGetLastError() != hipSuccess) return bfail(b, NGF_E_HIP, "batched evaluation launch");
     if (J) {

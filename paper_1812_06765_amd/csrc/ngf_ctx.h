@@ -143,7 +143,6 @@ struct Geo {
 Geo geometry(const Level& L, int variant);
 int tiles(int m, int t);
 int64_t node_blocks(const Level& L);
-int node_chunk(const Level& L);
 ngf_status fail(ngf_ctx* c, ngf_status s, const std::string& msg);
 
 // Arguments of the three kernels of one evaluation at level L of context c:
@@ -157,7 +156,6 @@ struct EvalArgs {
 EvalArgs eval_args(ngf_ctx* c, const Level& L, const float* R, const float* T, const float* y,
                    float* grad, const int* gate, LbState* decide);
 bool pow2(double h);
-void node_grid(const Level& L, int nb[3]);
 
 // Partial-sum buffers of the differentiation form (null: the context's own).
 struct ScatterBufs {

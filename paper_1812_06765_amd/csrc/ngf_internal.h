@@ -21,10 +21,24 @@ constexpr int kTX = 8, kTY = 8, kTZ = 32;
 // Marching image pass: (y, z) tile of kMY x (32 or 64); the x chunk is a
 // run-time choice.
 constexpr int kMY = 16;
-// Node pass: (y, z) tile of kNMY x kNMZ nodes, marching along x in a chunk
-// fitted to the grid and the device.
-constexpr int kNMY = 8, kNMZ = 32;
-constexpr int kNodeChunkMax = 256;  // node planes per node-pass workgroup, at most
+// Node pass, three forms by the grid's node count: 3D tiles of nodes, small or
+// larger ones, and (y, z) tiles marching along x in a chunk fitted to the grid
+// and the device.  Few nodes need small tiles, or most of the chip idles: 36 K
+// nodes take 8.5 us with 4 x 4 x 17 and 10.3 with 8 x 7 x 17; 118 K take 10.5
+// and 10.3, and 275 K 20 and 15 (20.5 marching), the small tiles' halos then
+// being the larger part of the work.  The marching form recomputes halos in
+// (y, z) only, but each workgroup is a chain of planes: 510 K nodes take 23.5
+// against 20.7 with the larger tiles, 2.1 M 35.6 against 60.
+struct NodeForm {
+    int x, y, z, threads;  // x = 0: marching
+};
+constexpr int kNodeForms = 3;
+constexpr NodeForm kNodeForm[kNodeForms] = {{4, 4, 17, 768}, {8, 7, 17, 1024}, {0, 15, 33, 512}};
+constexpr int64_t kNodeFrom1 = 100000, kNodeFrom2 = 1000000;
+constexpr int kNodeChunkMax = 256;  // node planes per marching workgroup, at most
+inline int node_form_of(int64_t nodes) {
+    return nodes < kNodeFrom1 ? 0 : nodes < kNodeFrom2 ? 1 : 2;
+}
 
 // Image-pass variants the autotuner chooses from: the 3D-tile kernel at three
 // tile sizes, and the marching kernel with in-plane tile 16 x 64 or 16 x 32
@@ -196,6 +210,7 @@ struct NodePassArgs {
     int mx, my, mz;        // image cells per axis (for the index maps)
     int px, py, pz;        // nodes per tile block of the image-pass partial sums
     int nbx, nby, nbz;     // node-pass blocks per axis
+    int form;              // of kNodeForm
     int cxn;               // x chunk of the marching form (node planes)
     double hyx, hyy, hyz;  // node spacing (float64, for X = j h^y)
     float ihy2x, ihy2y, ihy2z;  // 1 / (h^y)^2
@@ -320,7 +335,7 @@ void launch_image_pass_batch(const ImagePassArgs* args, const BlockRef* blk, int
                              int variant, bool pow2, hipStream_t s);
 void launch_image_march_batch(const ImagePassArgs* args, const BlockRef* blk, int nblk,
                               int ratio, int variant, bool pow2, hipStream_t s);
-void launch_node_pass_batch(const NodePassArgs* args, const BlockRef* blk, int nblk,
+void launch_node_pass_batch(const NodePassArgs* args, const BlockRef* blk, int nblk, int form,
                             hipStream_t s);
 void launch_reduce_batch(const ReduceArgs* args, int npairs, hipStream_t s);
 void launch_lb_init_batch(const LbVecArgs* args, int npairs, hipStream_t s);
