@@ -332,12 +332,13 @@ ngf_status ngf_register_levels(ngf_ctx* ctx, float* y_out, ngf_report* rep);
 
 /* Differentiation form (for an autograd wrapper): J(y; R, T) on an explicit
  * image pair (not the pyramid) and its gradients with respect to y and to
- * the template T.  The backward is a scatter: each image tile adds its P^T
- * block into grad_y with float atomic additions, and every image point adds
- * e[i] W(i -> k) into grad_T[k] for the 8 corners k of its warp cell (the
- * transpose of the trilinear warp, with e = G^T v the NGF sensitivity of
- * the warped template), so these gradients are reproducible only up to
- * rounding; alpha grad S is added by the node pass.  Sec. 2.1 (Eq. 1),
+ * the template T.  grad_y is the evaluation's own gather.  grad_T is a
+ * scatter: every image point adds e[i] W(i -> k) into grad_T[k] for the 8
+ * corners k of its warp cell (the transpose of the trilinear warp, with
+ * e = G^T v the NGF sensitivity of the warped template), summed per image
+ * tile and added with float atomics, so it is reproducible only up to
+ * rounding.  Where the scratch for e (one float per voxel) cannot be had, and
+ * for 2^30 voxels and more, grad_y is scattered with atomics too.  Sec. 2.1 (Eq. 1),
  * Sec. 2.2 (Eq. 2 and the matrix-free chain rule).
  *   g, my      image grid; my[d] must be m[d]/ratio + 1 (else NGF_E_SHAPE)
  *   R, T, y    device inputs in the usual layouts
@@ -356,8 +357,9 @@ ngf_status ngf_eval_pair(ngf_ctx* ctx, const ngf_grid* g, const int32_t my[3],
 
 /* ngf_eval_pair without any device allocation, for callers that cannot
  * allocate (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc).  Same arguments, kernels and results as
- * ngf_eval_pair; the pair's index maps and the partial sums live in a static
+ * that forbid hipMalloc).  Same arguments as ngf_eval_pair and the same
+ * results up to rounding (both gradients are scattered with float atomics,
+ * which needs no scratch per voxel); the pair's index maps and the partial sums live in a static
  * device array of 2 MiB per device (held until the process ends), so the
  * grid is limited to what fits there (about 512^3 voxels; larger grids get
  * NGF_E_SHAPE with the bytes needed).  The ratio is the context's (2 or 4).
@@ -375,8 +377,8 @@ ngf_status ngf_eval_pair_static(ngf_ctx* ctx, const ngf_grid* g, const int32_t m
 /* The differentiation form on a pyramid level (Sec. 2.1, Eq. 1; Sec. 2.2,
  * Eq. 2 and the matrix-free chain rule): J at y on level `level` with its
  * gradients with respect to y and to the level's template image, computed
- * as by ngf_eval_pair (atomic scatter of the P^T blocks and of e W(i -> k)
- * into the warp corners) but on the pyramid's images and index maps, with
+ * as by ngf_eval_pair_static (atomic scatter of the P^T blocks and of
+ * e W(i -> k) into the warp corners) but on the pyramid's images and index maps, with
  * buffers sized by ngf_build_pyramid: nothing is allocated, so the call can
  * be captured in a graph when J is NULL.
  *   y       device float32 deformation of the level

@@ -3,9 +3,9 @@ torch.autograd.Function.
 
 The forward and the hand-written backward both run in the HIP library
 (``ngf_eval_pair``): the backward recomputes the warp and the NGF
-sensitivity and scatters them with atomics into grad y (through P^T) and
-grad T (through the transpose of the trilinear warp), scaled on the device
-by the upstream gradient.  R is a constant of the objective.
+sensitivity and takes them through P^T to grad y and through the transpose of
+the trilinear warp (a scatter, summed per tile in LDS) to grad T, scaled on the
+device by the upstream gradient.  R is a constant of the objective.
 """
 
 from __future__ import annotations

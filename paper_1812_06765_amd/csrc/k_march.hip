@@ -56,6 +56,9 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const float* p, uint32_t byte
 __device__ inline float bload(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
+__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, float v, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, voff, soff, 0);
+}
 __device__ inline float2 bload2(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
     return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
@@ -197,7 +200,8 @@ __device__ inline double index_of(double yh, double h, double ih) {
     }
 }
 
-template <int TY, int TZ, int R, bool GRAD, bool POW2>
+// SENS: e is also stored, for the template gradient
+template <int TY, int TZ, int R, bool GRAD, bool POW2, bool SENS = false>
 __device__ __forceinline__ void march_body(const ImagePassArgs& a, int CX, int block) {
     using L = March<TY, TZ, R>;
     constexpr int NT = L::NT, H2Z = L::H2Z;
@@ -575,6 +579,13 @@ __device__ __forceinline__ void march_body(const ImagePassArgs& a, int CX, int b
                     eA = inside ? eA : 0.0f;
                     eB = inside ? eB : 0.0f;
                 }
+                if (SENS && inside) {
+                    const __amdgpu_buffer_rsrc_t rS =
+                        make_rsrc(a.sens, static_cast<uint32_t>(mx) * plane4);
+                    const uint32_t pe4 = static_cast<uint32_t>(pe) * plane4;
+                    bstore(rS, eA, offA, pe4);
+                    bstore(rS, eB, offA, pe4 + row4);
+                }
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     const float gA = eA * dA[S2][c], gB = eB * dB[S2][c];
@@ -656,6 +667,12 @@ __global__ __launch_bounds__((March<TY, TZ, R>::NT), 4) void k_image_march(
     march_body<TY, TZ, R, GRAD, POW2>(a, CX, blockIdx.x);
 }
 
+template <int TY, int TZ, int R, bool POW2>
+__global__ __launch_bounds__((March<TY, TZ, R>::NT), 4) void k_image_march_sens(
+    ImagePassArgs a, int CX) {
+    march_body<TY, TZ, R, true, POW2, true>(a, CX, blockIdx.x);
+}
+
 // Each pair's chunk length is its own (a.cx).  The pair and block indices
 // are uniform over the workgroup: taken as such, the pair's arguments load
 // into scalar registers and the kernel needs no more vector registers than
@@ -708,7 +725,32 @@ void launch_march_t(const ImagePassArgs& a, int cx, hipStream_t s) {
     }
 }
 
+template <int TY, int TZ, int R>
+void launch_march_sens_t(const ImagePassArgs& a, int cx, hipStream_t s) {
+    using L = March<TY, TZ, R>;
+    const dim3 g(a.ntx * a.nty * a.ntz), b(L::NT);
+    const size_t lds = sizeof(float) * L::LDS_GRAD;
+    if (a.pow2h)
+        hipLaunchKernelGGL((k_image_march_sens<TY, TZ, R, true>), g, b, lds, s, a, cx);
+    else
+        hipLaunchKernelGGL((k_image_march_sens<TY, TZ, R, false>), g, b, lds, s, a, cx);
+}
+
 }  // namespace
+
+void launch_image_march_sens(const ImagePassArgs& a, int ratio, int ty, int cx, hipStream_t s) {
+    if (ty == 32) {
+        if (ratio == 2)
+            launch_march_sens_t<32, 32, 2>(a, cx, s);
+        else
+            launch_march_sens_t<32, 32, 4>(a, cx, s);
+    } else {
+        if (ratio == 2)
+            launch_march_sens_t<kMY, 32, 2>(a, cx, s);
+        else
+            launch_march_sens_t<kMY, 32, 4>(a, cx, s);
+    }
+}
 
 // gradient form only (the batched rounds always want the gradient)
 void launch_image_march_batch(const ImagePassArgs* args, const BlockRef* blk, int nblk,

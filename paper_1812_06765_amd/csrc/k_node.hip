@@ -202,7 +202,7 @@ __device__ __forceinline__ void node_body(const NodePassArgs& a, int block) {
     double ssum = 0.0, gmax = 0.0, g2 = 0.0;
     const N n(t);
     if (n.on && y0 + n.y < ny && z0 + n.z < nz) {
-        const float sc = (!GATHER && a.gscale != nullptr) ? static_cast<float>(*a.gscale) : 1.0f;
+        const float sc = a.gscale != nullptr ? static_cast<float>(*a.gscale) : 1.0f;
         const int NP = a.px * a.py * a.pz, PYZ = a.py * a.pz;
         const int64_t xslab = static_cast<int64_t>(a.nty) * a.ntz * 3 * NP;
         const int64_t nn = static_cast<int64_t>(nx) * ny * nz;
@@ -252,7 +252,7 @@ __device__ __forceinline__ void node_body(const NodePassArgs& a, int block) {
                     const float ly = q[c * A::N + A::PZ] - 2.0f * au + q[c * A::N - A::PZ];
                     const float lz = q[c * A::N + 1] - 2.0f * au + q[c * A::N - 1];
                     const float aau = fmaf(lx, a.ihy2x, fmaf(ly, a.ihy2y, lz * a.ihy2z));
-                    const float g = fmaf(a.alpha_hbary * sc, aau, gd[c]);
+                    const float g = fmaf(a.alpha_hbary * sc, aau, GATHER ? sc * gd[c] : gd[c]);
                     a.grad[c * nn + k] = g;
                     gmax = fmax(gmax, static_cast<double>(fabsf(g)));
                     g2 += static_cast<double>(g) * static_cast<double>(g);
@@ -324,7 +324,7 @@ __device__ __forceinline__ void node_march_body(const NodePassArgs& a, int block
     const int auA = (ly + 1) * AZ + lz + 1, auC = (byC - 1) * AZ + bzC - 1;
     const double XA[2] = {static_cast<double>(cyA) * a.hyy, static_cast<double>(czA) * a.hyz};
     const double XC[2] = {static_cast<double>(cyC) * a.hyy, static_cast<double>(czC) * a.hyz};
-    const float sc = (!GATHER && a.gscale != nullptr) ? static_cast<float>(*a.gscale) : 1.0f;
+    const float sc = a.gscale != nullptr ? static_cast<float>(*a.gscale) : 1.0f;
 
     // places in the blocks of the image-tile partials: along x a table per
     // plane of the chunk, in (y, z) four offsets (j = 2 oy + oz: the second
@@ -450,7 +450,7 @@ __device__ __forceinline__ void node_march_body(const NodePassArgs& a, int block
                 if (GRAD) {
                     const float aau = lap(po > 0 ? aA[S2][c] : au, au, po + 1 < nx ? aA[S0][c] : au,
                                           A[-AZ], A[AZ], A[-1], A[1]);
-                    const float g = fmaf(a.alpha_hbary * sc, aau, gd[c]);
+                    const float g = fmaf(a.alpha_hbary * sc, aau, GATHER ? sc * gd[c] : gd[c]);
                     a.grad[c * nn + g0] = g;
                     gmax = fmax(gmax, static_cast<double>(fabsf(g)));
                     g2 += static_cast<double>(g) * static_cast<double>(g);

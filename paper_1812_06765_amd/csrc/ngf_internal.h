@@ -195,6 +195,7 @@ struct ImagePassArgs {
     float* gy_atomic;      // [3][my], accumulated in place (zeroed beforehand)
     float* gT_atomic;      // [mx][my][mz], accumulated in place (zeroed beforehand)
     const double* gscale;  // device scalar multiplying both (null: 1)
+    float* sens;           // e = dD/dT_y per voxel (marching form with SENS, launch_scatter_T)
     const int* gate;       // device flag: the pass does nothing when *gate == kOpNone (null: always run)
 };
 
@@ -357,6 +358,10 @@ void launch_image_cube_batch(const ImagePassArgs* args, const BlockRef* blk, int
                              bool pow2, hipStream_t s);
 void launch_image_march(const ImagePassArgs& a, int ratio, int ty, int tz, int cx,
                         hipStream_t s);
+// grad J of an evaluation, and e per voxel into a.sens (32-wide marching tiles)
+void launch_image_march_sens(const ImagePassArgs& a, int ratio, int ty, int cx, hipStream_t s);
+// dJ/dT, added into a.gT_atomic from a.sens
+void launch_scatter_T(const ImagePassArgs& a, hipStream_t s);
 void launch_image_gen(const ImagePassArgs& a, int cx, hipStream_t s);
 void launch_image_gen_batch(const ImagePassArgs* args, const BlockRef* blk, int nblk, bool pow2,
                             hipStream_t s);

@@ -2,7 +2,8 @@
 // scratch -- the pair's index maps and the partial sums of D, S and the
 // gradient norms -- lives in one static device array instead of buffers the
 // context allocates, for callers that cannot allocate (graph capture, tight
-// serving loops).  The kernels are those of ngf_eval_pair.
+// serving loops).  It takes the scattering kernels, whose scratch does not grow
+// by a value per voxel.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
