@@ -452,7 +452,8 @@ Tile64 gather_tile(const Grid64& g) {
 __global__ __launch_bounds__(kT) void k64_reduce(const double* __restrict__ dpart, int nd,
                                                  const double* __restrict__ spart, int ns,
                                                  double half_hbar, double half_hbary,
-                                                 double alpha, double* __restrict__ out) {
+                                                 double alpha, double* __restrict__ out,
+                                                 double* __restrict__ host) {
     __shared__ double red[2][kT / 64];
     double a = 0.0, b = 0.0;
 #pragma unroll 4
@@ -465,6 +466,11 @@ __global__ __launch_bounds__(kT) void k64_reduce(const double* __restrict__ dpar
         out[0] = D + alpha * S;
         out[1] = D;
         out[2] = S;
+        if (host) {  // pinned: no copy kernel behind this one
+            host[0] = out[0];
+            host[1] = D;
+            host[2] = S;
+        }
     }
 }
 
@@ -541,11 +547,11 @@ extern "C" ngf_status ngf_eval_J_grad_f64(ngf_ctx* c, int32_t level, const doubl
         k64_warp<false><<<nv + nl, kT, 0, s>>>(g, y, L.T, Ty, dT, Au, spart, nv);
         k64_ngf<false><<<nv, kT, 0, s>>>(g, Ty, L.R, c->p.tau, c->p.rho, hbar, v, dpart);
     }
-    k64_reduce<<<1, kT, 0, s>>>(dpart, nv, spart, nl, 0.5 * hbar, 0.5 * hbary, c->p.alpha, out);
+    k64_reduce<<<1, kT, 0, s>>>(dpart, nv, spart, nl, 0.5 * hbar, 0.5 * hbary, c->p.alpha, out,
+                               J || DS ? c->host_jds : nullptr);
     F64CHK(c, hipGetLastError());
     if (J || DS) {
-        double h3[3];
-        F64CHK(c, hipMemcpyAsync(h3, out, sizeof(h3), hipMemcpyDeviceToHost, s));
+        const double* h3 = c->host_jds;
         F64CHK(c, hipStreamSynchronize(s));
         if (J) *J = h3[0];
         if (DS) {

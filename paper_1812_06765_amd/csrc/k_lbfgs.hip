@@ -20,9 +20,9 @@ namespace ngf {
 namespace {
 
 __global__ void k_lb_init(LbState* st, int mem, double hmin, const double* jds, int max_iter,
-                          int early_stop, double tol) {
+                          int early_stop, double tol, int reject) {
     if (threadIdx.x == 0 && blockIdx.x == 0)
-        lb_init_one(st, mem, hmin, jds, max_iter, early_stop, tol);
+        lb_init_one(st, mem, hmin, jds, max_iter, early_stop, tol, reject);
 }
 
 __global__ void k_lb_solve(LbState* st, double* jds) {
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kGramThreads) void k_lb_gram_plan(LbState* st,
 __global__ void k_lb_init_batch(const LbVecArgs* args) {
     const LbVecArgs& a = args[blockIdx.x];
     if (threadIdx.x == 0)
-        lb_init_one(a.st, a.mem, a.hmin, a.jds, a.max_iter, a.early_stop, a.tol);
+        lb_init_one(a.st, a.mem, a.hmin, a.jds, a.max_iter, a.early_stop, a.tol, 0);
 }
 
 __global__ void k_lb_plan_batch(const LbVecArgs* args) {
@@ -224,9 +224,9 @@ int lb_dot_blocks(int64_t n) {
 }
 
 void launch_lb_init(LbState* st, int mem, double hmin, const double* jds, int max_iter,
-                    int early_stop, double tol, hipStream_t s) {
+                    int early_stop, double tol, int reject, hipStream_t s) {
     hipLaunchKernelGGL(k_lb_init, dim3(1), dim3(64), 0, s, st, mem, hmin, jds, max_iter,
-                       early_stop, tol);
+                       early_stop, tol, reject);
 }
 
 void launch_lb_solve(LbState* st, double* jds, hipStream_t s) {

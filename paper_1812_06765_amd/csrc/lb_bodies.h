@@ -59,7 +59,7 @@ __device__ inline double lb_wave_sum(double v) {
 }
 
 __device__ inline void lb_init_one(LbState* st, int mem, double hmin, const double* jds,
-                                   int max_iter, int early_stop, double tol) {
+                                   int max_iter, int early_stop, double tol, int reject) {
     LbCtl& c = st->ctl;
     c.op = kOpNone;
     c.phase = kPhNeedDir;
@@ -89,7 +89,7 @@ __device__ inline void lb_init_one(LbState* st, int mem, double hmin, const doub
     for (int i = 0; i < kBasis * kBasis; ++i) st->G[i] = 0.0;
     for (int i = 0; i < kBasis; ++i) st->coef[i] = 0.0;
     st->G[kBasisG * kBasis + kBasisG] = jds[4];
-    st->reject_all = 0;  // failure injection: set by the host after this kernel
+    st->reject_all = reject;  // failure injection
 }
 
 // Direction coefficients by the two-loop recursion over the Gram matrix.

@@ -421,12 +421,20 @@ EvalArgs eval_args(ngf_ctx* c, const Level& L, const float* R, const float* T, c
     return e;
 }
 
+// Where the final reduction also puts its results (see ReduceArgs).
+struct Results {
+    double* host = nullptr;
+    double* jdev = nullptr;
+};
+
 // Enqueue one evaluation on the context stream; results land in c->jds and
 // (if grad != nullptr) in grad.
 ngf_status enqueue_eval(ngf_ctx* c, const Level& L, const float* R, const float* T,
                         const float* y, float* grad, const int* gate = nullptr,
-                        LbState* decide = nullptr) {
-    const EvalArgs e = eval_args(c, L, R, T, y, grad, gate, decide);
+                        LbState* decide = nullptr, const Results& to = {}) {
+    EvalArgs e = eval_args(c, L, R, T, y, grad, gate, decide);
+    e.r.host = to.host;
+    e.r.jdev = to.jdev;
     auto launch = [&] {
         if (is_gen(L.variant))
             launch_image_gen(e.a, e.a.cx, c->stream);
@@ -698,17 +706,19 @@ ngf_status check_level(const ngf_ctx* c, int level) {
 }
 
 
-// J of the evaluation just queued: copied to J_dev (device) and read back to
-// J (host, synchronises) when given.
-ngf_status finish_J(ngf_ctx* c, double* J, double* J_dev) {
-    if (J_dev)
-        HIPCHK(c, hipMemcpyAsync(J_dev, c->jds, sizeof(double), hipMemcpyDeviceToDevice,
-                                 c->stream));
-    if (J) {
-        if (read_jds(c) != NGF_OK) return NGF_E_HIP;
-        *J = c->host_jds[0];
-        if (!std::isfinite(*J)) return fail(c, NGF_E_NONFINITE, "J is not finite");
-    }
+// Where J of an evaluation goes: to J_dev (device) and to the host if it is
+// wanted there.
+Results results_to(ngf_ctx* c, const double* J, double* J_dev) {
+    return {J ? c->host_jds : nullptr, J_dev};
+}
+
+// J of the evaluation just queued (with results_to), read on the host
+// (synchronises) when wanted.
+ngf_status finish_J(ngf_ctx* c, double* J) {
+    if (!J) return NGF_OK;
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    *J = c->host_jds[0];
+    if (!std::isfinite(*J)) return fail(c, NGF_E_NONFINITE, "J is not finite");
     return NGF_OK;
 }
 
@@ -726,6 +736,8 @@ ngf_status eval_diff(ngf_ctx* c, const Level& P, const float* R, const float* T,
     EvalArgs e = eval_args(c, V, R, T, y, grad_y, nullptr, nullptr);
     e.a.want_grad = 1;
     e.a.gscale = e.b.gscale = gscale;
+    e.r.host = results_to(c, J, J_dev).host;
+    e.r.jdev = J_dev;
     if (grad_T) {
         e.a.sens = c->part + part_floats(P, V.variant);
         e.a.gT_atomic = grad_T;
@@ -744,7 +756,7 @@ ngf_status eval_diff(ngf_ctx* c, const Level& P, const float* R, const float* T,
     HIPCHK(c, hipGetLastError());
     launch_reduce(e.r, c->stream);
     HIPCHK(c, hipGetLastError());
-    return finish_J(c, J, J_dev);
+    return finish_J(c, J);
 }
 
 // Differentiation form on level L (its grids and index maps) with images R, T:
@@ -766,9 +778,10 @@ ngf_status eval_scatter(ngf_ctx* c, const Level& P, const float* R, const float*
         Level V = P;
         const int v = variant_by_size(V);
         V.variant = variant_ok(V, v) && march_fits(V) ? v : P.variant;
-        const ngf_status e = enqueue_eval(c, V, R, T, y, nullptr);
+        const ngf_status e = enqueue_eval(c, V, R, T, y, nullptr, nullptr, nullptr,
+                                          results_to(c, J, J_dev));
         if (e != NGF_OK) return e;
-        return finish_J(c, J, J_dev);
+        return finish_J(c, J);
     }
     if (grad_y) launch_fill(grad_y, 3 * P.Ny(), 0.0f, c->stream);
     if (grad_T) launch_fill(grad_T, P.N(), 0.0f, c->stream);
@@ -824,9 +837,11 @@ ngf_status eval_scatter(ngf_ctx* c, const Level& P, const float* R, const float*
     rd.half_hbary = 0.5 * hbary;
     rd.alpha = c->p.alpha;
     rd.out = c->jds;
+    rd.host = results_to(c, J, J_dev).host;
+    rd.jdev = J_dev;
     launch_reduce(rd, c->stream);
     HIPCHK(c, hipGetLastError());
-    return finish_J(c, J, J_dev);
+    return finish_J(c, J);
 }
 
 }  // namespace ngf_host
@@ -1130,10 +1145,12 @@ ngf_status ngf_eval_J_grad(ngf_ctx* c, int32_t level, const float* y, double* J,
     if (s != NGF_OK) return fail(c, s, "no pyramid or bad level");
     if (!y) return fail(c, NGF_E_ARG, "null y");
     const Level& L = c->lv[level];
-    ngf_status e = enqueue_eval(c, L, L.R, L.T, y, grad);
+    const bool read = J || DS;
+    ngf_status e = enqueue_eval(c, L, L.R, L.T, y, grad, nullptr, nullptr,
+                                {read ? c->host_jds : nullptr, nullptr});
     if (e != NGF_OK) return e;
-    if (J || DS) {
-        if (read_jds(c) != NGF_OK) return NGF_E_HIP;
+    if (read) {
+        HIPCHK(c, hipStreamSynchronize(c->stream));
         if (J) *J = c->host_jds[0];
         if (DS) {
             DS[0] = c->host_jds[1];
@@ -1160,16 +1177,14 @@ ngf_status ngf_lbfgs_reset(ngf_ctx* c, int32_t level, const float* y0) {
     if (y0 != c->ly)
         HIPCHK(c, hipMemcpyAsync(c->ly, y0, n * sizeof(float), hipMemcpyDeviceToDevice,
                                  c->stream));
-    ngf_status e = enqueue_eval(c, L, L.R, L.T, c->ly, c->lg);
+    ngf_status e = enqueue_eval(c, L, L.R, L.T, c->ly, c->lg, nullptr, nullptr,
+                                {c->host_jds, nullptr});
     if (e != NGF_OK) return e;
     const double hmin = std::min(L.h[0], std::min(L.h[1], L.h[2]));
     launch_lb_init(c->st, c->p.lbfgs_mem, hmin, c->jds, c->p.max_iter, c->p.early_stop,
-                   c->p.tol_J, c->stream);
+                   c->p.tol_J, (c->faults & NGF_FAULT_REJECT_STEPS) ? 1 : 0, c->stream);
     HIPCHK(c, hipGetLastError());
-    const int reject = (c->faults & NGF_FAULT_REJECT_STEPS) ? 1 : 0;
-    HIPCHK(c, hipMemcpyAsync(&c->st->reject_all, &reject, sizeof(int), hipMemcpyHostToDevice,
-                             c->stream));
-    if (read_jds(c) != NGF_OK) return NGF_E_HIP;
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     c->lb_level = level;
     c->lb_J = c->host_jds[0];
     c->lb_gmax = c->host_jds[3];

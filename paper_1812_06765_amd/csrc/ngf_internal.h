@@ -231,6 +231,8 @@ struct ReduceArgs {
     const double* gpart; int ng;   // pairs (max, sumsq); ng == 0: skip
     double half_hbar, half_hbary, alpha;
     double* out;                    // {J, D, S, max|g|, |g|^2}
+    double* host;                   // the same in pinned host memory (null: not wanted)
+    double* jdev;                   // J in the caller's device memory (null: not wanted)
     const int* gate;                // as in ImagePassArgs
     LbState* lb;                    // device-driven level: Armijo test of J (null: none)
 };
@@ -402,7 +404,7 @@ void launch_lb_update_dots(LbState* st, float* hist, int64_t ld, int64_t n, cons
 void launch_lb_gram_update(LbState* st, const double* dotpart, int nblocks,
                            const double* jds, hipStream_t s);
 void launch_lb_init(LbState* st, int mem, double hmin, const double* jds, int max_iter,
-                    int early_stop, double tol, hipStream_t s);
+                    int early_stop, double tol, int reject, hipStream_t s);
 int lb_dot_blocks(int64_t n);
 
 

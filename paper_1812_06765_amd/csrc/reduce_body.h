@@ -62,6 +62,16 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs& a) {
         // with the non-finite outcome
         a.out[3] = isfinite(g2) ? gm : g2;
         a.out[4] = g2;
+        // written here, the host's copy and the caller's J need no copy kernel
+        // (4 us and a gap) behind this one
+        if (a.host) {
+            a.host[0] = J;
+            a.host[1] = D;
+            a.host[2] = S;
+            a.host[3] = a.out[3];
+            a.host[4] = g2;
+        }
+        if (a.jdev) *a.jdev = J;
         if (a.lb) lb_decide_one(a.lb, J);
     }
 }
