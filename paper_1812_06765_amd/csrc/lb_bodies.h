@@ -53,9 +53,44 @@ __device__ inline void lb_st4(float* p, int64_t q, float4 v) {
     }
 }
 
-__device__ inline double lb_wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return v;
+// One step of lb_wave_sums: lanes without the bit MASK get a(l) + a(l ^ MASK),
+// the others b(l) + b(l ^ MASK).
+template <int MASK>
+__device__ inline double lb_fold(double a, double b) {
+    if constexpr (MASK >= 16) {
+        const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+        uint64_t x = 0, y = 0;
+#pragma unroll
+        for (int h = 0; h < 64; h += 32) {
+            const uint32_t p = static_cast<uint32_t>(ua >> h), q = static_cast<uint32_t>(ub >> h);
+            const auto r = MASK == 32 ? __builtin_amdgcn_permlane32_swap(p, q, false, false)
+                                      : __builtin_amdgcn_permlane16_swap(p, q, false, false);
+            x |= static_cast<uint64_t>(r[0]) << h;
+            y |= static_cast<uint64_t>(r[1]) << h;
+        }
+        return __longlong_as_double(x) + __longlong_as_double(y);
+    } else {
+        const bool up = threadIdx.x & MASK;
+        const double give = up ? a : b, keep = up ? b : a;
+        return keep + __shfl_xor(give, MASK, 64);
+    }
+}
+
+// Sums of M values over the wave at once: each step folds the lanes in two and
+// leaves each half with half of the values, so a few lane exchanges do
+// what M separate trees of 6 would (38 for 36 values, against 216).  A lane
+// ends with the sum of value j in v[0] if left > 0.  The pairs added are those
+// of the tree from lane l + 32 down to l + 1.  The history update of 10^5
+// unknowns, which these sums dominate, 8.9 -> 4.6 us.
+template <int MASK, int M, int N>
+__device__ __forceinline__ void lb_wave_sums(double (&v)[N], int& j, int& left) {
+    constexpr int H = (M + 1) / 2;
+#pragma unroll
+    for (int i = 0; i < H; ++i) v[i] = lb_fold<MASK>(v[i], i + H < M ? v[i + H] : 0.0);
+    const bool up = threadIdx.x & MASK;
+    j += up ? H : 0;
+    left = up ? left - H : min(left, H);
+    if constexpr (MASK > 1) lb_wave_sums<MASK / 2, H>(v, j, left);
 }
 
 __device__ inline void lb_init_one(LbState* st, int mem, double hmin, const double* jds,
@@ -114,29 +149,45 @@ __device__ inline void lb_stage(const LbState* st, SolveLds& w) {
     __syncthreads();
 }
 
-// Sum over the 64 lanes of a wave by a butterfly: every lane ends with the
-// same value (each step adds a + b and b + a, which round alike).
-__device__ inline double lb_wave_allsum(double v) {
-    for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-    return v;
+// v moved within rows of 16 lanes by a DPP control.
+template <int CTRL>
+__device__ inline double lb_dpp(double v) {
+    const uint64_t b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 |
+                                static_cast<uint32_t>(lo));
+}
+__device__ inline double lb_lane(double v, int lane) {
+    const uint64_t b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(b), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(b >> 32), lane);
+    return __longlong_as_double(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
+// Sum over the first kBasis lanes (the others hold 0), the same value in every
+// lane: two rows of 16 by exchanges within them, then their sums.
+__device__ inline double lb_basis_sum(double v) {
+    static_assert(kBasis <= 32, "two rows of 16 lanes");
+    double r = v + lb_dpp<0xB1>(v);  // xor 1
+    r += lb_dpp<0x4E>(r);            // xor 2
+    r += lb_dpp<0x141>(r);           // the other quad of the half row
+    r += lb_dpp<0x140>(r);           // the other half row
+    return lb_lane(r, 0) + lb_lane(r, 16);
 }
 
 // The recursion on one wave: lane l < kBasis holds the coefficient q_l of
-// basis vector l, each inner product q^T G e_i is a wave sum, and the scalars
-// of the recursion (every lane computes them alike) stay in registers; lane k
-// keeps alpha_k for the second loop.  The g^T g entry of G refers to the
-// current gradient: it is read as such here and set in the state.  Called by
-// every lane of the block's first wave.
+// basis vector l, each inner product q^T G e_i is a sum over those lanes, and
+// the scalars of the recursion are the same in every lane; lane k keeps alpha_k
+// for the second loop.  It is one chain of dependent sums, so what does not
+// depend on it comes first: the rows of G, and 1 / s_k^T t_k (lane k); the sums
+// are by DPP.  Gram update and recursion of a round 7.2 -> 5.8 us.  The g^T g
+// entry of G refers to the current gradient: it is read as such here and set in
+// the state.  Called by every lane of the block's first wave.
 __device__ inline void lb_solve_wave(LbState* st, double* jds, SolveLds& w) {
     const int l = threadIdx.x & 63;
     const double* G = w.G;
     const double gn2 = st->gnorm2;
-    auto Gat = [&](int i, int j) {
-        return (i == kBasisG && j == kBasisG) ? gn2 : G[i * kBasis + j];
-    };
-    auto row_dot = [&](double q, int i) {  // sum_l q_l G(i, l)
-        return lb_wave_allsum(l < kBasis ? q * Gat(i, l) : 0.0);
-    };
     const double gmax = st->gmax, hmin = st->hmin;
     int count = st->count;
     if (l == 0) st->G[kBasisG * kBasis + kBasisG] = gn2;
@@ -151,24 +202,38 @@ __device__ inline void lb_solve_wave(LbState* st, double* jds, SolveLds& w) {
     }
     double flags = 0.0, gtd = 0.0, q = 0.0;
     if (count > 0) {
+        auto row = [&](int i) { return l < kBasis ? G[i * kBasis + l] : 0.0; };
+        int slot[kSlots];
+        double rs[kSlots], rt[kSlots];
+#pragma unroll
+        for (int k = 0; k < kSlots; ++k) {
+            slot[k] = __builtin_amdgcn_readfirstlane(k < count ? w.order[k] : 0);
+            rs[k] = row(slot[k]);
+            rt[k] = row(kSlots + slot[k]);
+        }
+        const double rg = l == kBasisG ? gn2 : row(kBasisG);
+        const int own = l < count ? w.order[l] : w.order[0];
+        const double inv = 1.0 / G[own * kBasis + kSlots + own];
         q = l == kBasisG ? 1.0 : 0.0;
         double al = 0.0;
-        for (int k = count - 1; k >= 0; --k) {
-            const int si = w.order[k], ti = kSlots + si;
-            const double a = row_dot(q, si) / Gat(si, ti);
+#pragma unroll
+        for (int k = kSlots - 1; k >= 0; --k) {
+            if (k >= count) continue;
+            const double a = lb_basis_sum(q * rs[k]) * lb_lane(inv, k);
             if (l == k) al = a;
-            if (l == ti) q -= a;
+            if (l == kSlots + slot[k]) q -= a;
         }
         const int sn = w.order[count - 1], tn = kSlots + sn;
-        q *= Gat(sn, tn) / Gat(tn, tn);
-        for (int k = 0; k < count; ++k) {
-            const int si = w.order[k], ti = kSlots + si;
-            const double b = row_dot(q, ti) / Gat(si, ti);
-            const double a = __shfl(al, k, 64);
-            if (l == si) q += a - b;
+        q *= G[sn * kBasis + tn] / G[tn * kBasis + tn];
+#pragma unroll
+        for (int k = 0; k < kSlots; ++k) {
+            if (k >= count) continue;
+            const double b = lb_basis_sum(q * rt[k]) * lb_lane(inv, k);
+            const double a = lb_lane(al, k);
+            if (l == slot[k]) q += a - b;
         }
         q = -q;  // the coefficients of d
-        gtd = row_dot(q, kBasisG);
+        gtd = lb_basis_sum(q * rg);
         if (!(gtd < 0.0)) {
             count = 0;
             flags = 1.0;
@@ -374,12 +439,9 @@ __device__ __forceinline__ void lb_dots_pass(const int* sl, int fs, float* __res
     }
     // wave sums, then the four waves in a fixed order; dots of unused slots are 0
     const int w = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < kA; ++j) {
-        const double v = lb_wave_sum(acc[j]);
-        const int o = j < 6 * C ? j : 6 * kSlots + (j - 6 * C);
-        if ((threadIdx.x & 63) == 0) sh[w][o] = v;
-    }
+    int j = 0, left = kA;
+    lb_wave_sums<32, kA>(acc, j, left);
+    if (left > 0) sh[w][j < 6 * C ? j : 6 * kSlots + (j - 6 * C)] = acc[0];
     for (int o = 6 * C + threadIdx.x; o < 6 * kSlots; o += kThreads)
         sh[0][o] = sh[1][o] = sh[2][o] = sh[3][o] = 0.0;
     __syncthreads();
@@ -440,7 +502,7 @@ constexpr int kGramThreads = 1024;
 
 constexpr int kGramPhases = kGramThreads / 64;
 
-__device__ __forceinline__ void lb_gram_one(LbState* st, const double* dots, const double* jds);
+__device__ __forceinline__ void lb_gram_wave(LbState* st, const double* dots, const double* jds);
 
 __device__ __forceinline__ void lb_gram_body(LbState* st,
                                                                  const double* dotpart,
@@ -469,15 +531,16 @@ __device__ __forceinline__ void lb_gram_body(LbState* st,
         dots[threadIdx.x] = s;
     }
     __syncthreads();
-    if (threadIdx.x == 0) lb_gram_one(st, dots, jds);
+    if (threadIdx.x < 64) lb_gram_wave(st, dots, jds);
 }
 
-// The Gram update itself (one lane): curvature test of the new pair, ring
-// update, new entries of G.
-__device__ __forceinline__ void lb_gram_one(LbState* st, const double* dots, const double* jds) {
+// The Gram update itself (one wave, a lane per stored pair): curvature test of
+// the new pair, ring update, new entries of G.
+__device__ __forceinline__ void lb_gram_wave(LbState* st, const double* dots, const double* jds) {
+    const int l = threadIdx.x;
     double* G = st->G;
     const int count = st->count;
-    const int fs = st->free_slot;
+    const int fs = st->free_slot, mem = st->mem;
     const double ss = dots[6 * kSlots + 0], sz = dots[6 * kSlots + 1],
                  sg = dots[6 * kSlots + 2], zz = dots[6 * kSlots + 3],
                  zg = dots[6 * kSlots + 4], gg = dots[6 * kSlots + 5];
@@ -486,50 +549,58 @@ __device__ __forceinline__ void lb_gram_one(LbState* st, const double* dots, con
         G[i * kBasis + j] = v;
         G[j * kBasis + i] = v;
     };
-    // the gradient row refers to the new gradient from now on
-    for (int k = 0; k < count; ++k) {
-        const int s = st->order[k];
-        setg(kBasisG, s, dots[6 * k + 4]);
-        setg(kBasisG, kSlots + s, dots[6 * k + 5]);
+    const int S = fs, T = kSlots + fs;
+    const bool stored = l < count;
+    const int s = stored ? st->order[l] : 0;
+    if (stored) {
+        // the gradient row refers to the new gradient from now on
+        setg(kBasisG, s, dots[6 * l + 4]);
+        setg(kBasisG, kSlots + s, dots[6 * l + 5]);
+        if (accept) {
+            setg(S, s, dots[6 * l + 0]);
+            setg(S, kSlots + s, dots[6 * l + 1]);
+            setg(T, s, dots[6 * l + 2]);
+            setg(T, kSlots + s, dots[6 * l + 3]);
+        }
     }
-    setg(kBasisG, kBasisG, gg);
+    if (l == 0) {
+        setg(kBasisG, kBasisG, gg);
+        if (accept) {
+            setg(S, S, ss);
+            setg(S, T, sz);
+            setg(T, T, zz);
+            setg(kBasisG, S, sg);
+            setg(kBasisG, T, zg);
+        }
+    }
+    int c = count;
     if (accept) {
-        const int S = fs, T = kSlots + fs;
-        for (int k = 0; k < count; ++k) {
-            const int s = st->order[k];
-            setg(S, s, dots[6 * k + 0]);
-            setg(S, kSlots + s, dots[6 * k + 1]);
-            setg(T, s, dots[6 * k + 2]);
-            setg(T, kSlots + s, dots[6 * k + 3]);
-        }
-        setg(S, S, ss);
-        setg(S, T, sz);
-        setg(T, T, zz);
-        setg(kBasisG, S, sg);
-        setg(kBasisG, T, zg);
-        int c = count;
-        if (c == st->mem) {  // drop the oldest pair
-            for (int k = 1; k < c; ++k) st->order[k - 1] = st->order[k];
-            c -= 1;
-        }
-        st->order[c] = fs;
-        st->count = c + 1;
+        const bool full = c == mem;  // drop the oldest pair
+        if (full) c -= 1;
+        if (full && stored && l > 0) st->order[l - 1] = s;
+        if (l == 0) st->order[c] = fs;
+        c += 1;
         // next free slot: the lowest slot not in use
-        for (int s = 0; s < kSlots; ++s) {
-            bool used = false;
-            for (int k = 0; k < st->count; ++k) used |= (st->order[k] == s);
-            if (!used) {
-                st->free_slot = s;
-                break;
-            }
+        uint32_t used = 1u << fs;
+#pragma unroll
+        for (int k = 0; k < kSlots; ++k) {
+            const int sk = __builtin_amdgcn_readlane(s, k);
+            if (k < count && !(full && k == 0)) used |= 1u << sk;
+        }
+        const uint32_t none = ~used & ((1u << kSlots) - 1);
+        if (l == 0) {
+            st->count = c;
+            if (none) st->free_slot = __builtin_ctz(none);
         }
     }
-    st->count_d = static_cast<double>(st->count);
-    st->J = jds[0];
-    st->D = jds[1];
-    st->S = jds[2];
-    st->gmax = jds[3];
-    st->gnorm2 = jds[4];
+    if (l == 0) {
+        st->count_d = static_cast<double>(c);
+        st->J = jds[0];
+        st->D = jds[1];
+        st->S = jds[2];
+        st->gmax = jds[3];
+        st->gnorm2 = jds[4];
+    }
 }
 
 // ---------------------------------------------------------------------------
