@@ -117,8 +117,10 @@ Geo geometry(const Level& L, int variant) {
         g.tz = march_tz(variant);
         g.tx = march_cx(variant);
         if (g.tx == 0)
-            g.tx = fit_chunk(L.m[0], int64_t{tiles(L.m[1], g.ty)} * tiles(L.m[2], g.tz), 4, 4,
-                             image_march_slots(g.ty, g.tz));
+            g.tx = L.chunk > 0
+                       ? std::min(L.chunk, tiles(L.m[0], 4) * 4)
+                       : fit_chunk(L.m[0], int64_t{tiles(L.m[1], g.ty)} * tiles(L.m[2], g.tz), 4,
+                                   4, image_march_slots(g.ty, g.tz));
     }
     g.ntx = tiles(L.m[0], g.tx);
     g.nty = tiles(L.m[1], g.ty);
@@ -139,6 +141,34 @@ Geo geometry(const Level& L, int variant) {
     }
     return g;
 }
+// As fit_chunk, for one launch over many levels: the rounds of all their
+// workgroups times the planes of the longest chunk.  A level's chunks are of like
+// length.
+void batch_chunks(const std::vector<Level*>& levels, int variant) {
+    const int slots = image_march_slots(march_ty(variant), march_tz(variant));
+    int len = 4;
+    auto chunk = [](const Level& L, int target) {
+        const int k = tiles(L.m[0], target);
+        return tiles(tiles(L.m[0], k), 4) * 4;
+    };
+    for (const Level* L : levels) len = std::max(len, tiles(L->m[0], 4) * 4);
+    int best = 4;
+    int64_t best_cost = -1;
+    for (int target = 4; target <= len; target += 4) {
+        int64_t n = 0;
+        int longest = 0;
+        for (const Level* L : levels) {
+            const int cx = chunk(*L, target);
+            longest = std::max(longest, cx);
+            n += int64_t{tiles(L->m[0], cx)} * tiles(L->m[1], march_ty(variant)) *
+                 tiles(L->m[2], march_tz(variant));
+        }
+        const int64_t cost = (n + slots - 1) / slots * (longest + 4);
+        if (best_cost < 0 || cost < best_cost) best = target, best_cost = cost;
+    }
+    for (Level* L : levels) L->chunk = chunk(*L, best);
+}
+
 int64_t part_floats(const Level& L, int variant) {
     const Geo g = geometry(L, variant);
     return g.ntiles() * 3 * int64_t{g.px} * g.py * g.pz;
@@ -218,6 +248,13 @@ ngf_status ensure_scratch(ngf_ctx* c, const Level& L, size_t floats = 0) {
         c->nblk_cap = nb;
     }
     return NGF_OK;
+}
+
+ngf_status ensure_level_scratch(ngf_ctx* c, const Level& L) {
+    const bool fits = static_cast<size_t>(part_floats(L, L.variant)) <= c->part_cap &&
+                      static_cast<size_t>(geometry(L, L.variant).ntiles()) <= c->dpart_cap &&
+                      static_cast<size_t>(node_blocks(L)) <= c->nblk_cap;
+    return fits ? NGF_OK : ensure_scratch(c, L);
 }
 
 ngf_status ensure_lbfgs(ngf_ctx* c, size_t n) {
@@ -527,11 +564,12 @@ void tune_cache_store(const std::string& key, int v) {
 // 58 / 57, 256^3 892 / 208 / 204: a small level has too few marching
 // workgroups to fill the device and is bound by their chain of planes, a
 // large one by the halo's work.
-int variant_by_size(const Level& L) {
+int variant_for(const Level& L, int64_t voxels) {
     if (!L.dyadic) return kMarchGen;
-    if (L.N() >= (int64_t{1} << 20)) return kMarchSqFit;
-    return L.N() >= 3 * (int64_t{1} << 17) ? kMarch32Fit : kTile3DTiny;
+    if (voxels >= (int64_t{1} << 20)) return kMarchSqFit;
+    return voxels >= 3 * (int64_t{1} << 17) ? kMarch32Fit : kTile3DTiny;
 }
+int variant_by_size(const Level& L) { return variant_for(L, L.N()); }
 
 // Image-pass variant of the differentiation form where the template gradient
 // is wanted: the marching tiles store the sensitivities it needs.

@@ -52,7 +52,7 @@ struct ngf_batch {
     ngf_params p{};
     int device = 0;
     int mode = 0;          // 0 graph, 1 worker threads
-    int variant = -3;      // -3: the mode's default (graph: timed, threads: size rule)
+    int variant = -3;      // -3: the mode's default (size rule, graph: over the batch)
     std::vector<Worker> workers;
     hipStream_t stream = nullptr;
     hipEvent_t start = nullptr;
@@ -76,7 +76,7 @@ ngf_status bfail(ngf_batch* b, ngf_status s, const std::string& m) {
     return s;
 }
 
-int graph_variant(const ngf_batch* b) { return b->variant == -3 ? -1 : b->variant; }
+int graph_variant(const ngf_batch* b) { return b->variant == -3 ? kVariantBySize : b->variant; }
 int thread_variant(const ngf_batch* b) { return b->variant == -3 ? kVariantBySize : b->variant; }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -133,6 +133,28 @@ ngf_status build_pairs(ngf_batch* b, int np, const float* const* R, const float*
         const ngf_status s = ngf_build_pyramid(c, R[i], T[i], &grids[i], 0);
         if (s != NGF_OK) return bfail(b, s, "pair " + std::to_string(i) + ": " + c->err);
         b->tune = c->tune_cache;
+    }
+    // Default selection: one launch covers all pairs of a level, so the size
+    // rule takes the voxels of all of them, and their chunks along x are chosen
+    // together: longer ones than a pair alone would take, with fewer halo planes.
+    // Twelve pairs of 96 to 160 points an axis: image passes of a registration
+    // 8.0 -> 5.5 ms against the selection timed pair by pair, which split a
+    // level over up to four variants' launches.
+    for (int lev = 0; b->variant == -3 && lev < b->p.levels; ++lev) {
+        int64_t total = 0;
+        for (int i = 0; i < np; ++i) total += b->pctx[i]->lv[lev].N();
+        std::vector<Level*> march;
+        for (int i = 0; i < np; ++i) {
+            Level& L = b->pctx[i]->lv[lev];
+            L.variant = variant_for(L, total);
+            if (is_march(L.variant)) march.push_back(&L);
+        }
+        if (!march.empty()) batch_chunks(march, march[0]->variant);
+        for (int i = 0; i < np; ++i) {
+            const Level& L = b->pctx[i]->lv[lev];
+            if (const ngf_status s = ensure_level_scratch(b->pctx[i], L); s != NGF_OK)
+                return bfail(b, s, "pair " + std::to_string(i) + ": " + b->pctx[i]->err);
+        }
     }
     b->nbuilt = np;
     return NGF_OK;
