@@ -19,17 +19,18 @@ inline int grid_for(int64_t n, int per_block = kThreads, int cap = 65536) {
 // One pyramid step: coarse voxel = mean of its 8 children, summed in float64
 // in the fixed order ((000+001)+(010+011)) + ((100+101)+(110+111)) and
 // rounded once to float32.  Contraction is off so the order is exactly this.
-__global__ __launch_bounds__(kThreads) void k_downsample(const float* __restrict__ src,
-                                                         float* __restrict__ dst, int mx,
-                                                         int my, int mz) {
+// R and T (blockIdx.y) in one launch.
+__global__ __launch_bounds__(kThreads) void k_downsample(ImagePair p, int mx, int my, int mz) {
 #pragma clang fp contract(off)
-    const int cx = mx / 2, cy = my / 2, cz = mz / 2;
-    const int64_t n = static_cast<int64_t>(cx) * cy * cz;
+    const float* __restrict__ src = p.src[blockIdx.y];
+    float* __restrict__ dst = p.dst[blockIdx.y];
+    const uint32_t cy = my / 2, cz = mz / 2;
+    const uint32_t n = static_cast<uint32_t>(mx / 2) * cy * cz;  // below 2^27
     const int64_t sy = mz, sx = static_cast<int64_t>(my) * mz;
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int z = static_cast<int>(i % cz);
-        const int64_t t = i / cz;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += gridDim.x * blockDim.x) {
+        const uint32_t t = i / cz;
+        const int z = static_cast<int>(i - t * cz);
         const int y = static_cast<int>(t % cy);
         const int x = static_cast<int>(t / cy);
         const float* p = src + (2 * x) * sx + (2 * y) * sy + 2 * z;
@@ -43,8 +44,7 @@ __global__ __launch_bounds__(kThreads) void k_downsample(const float* __restrict
 // Per-axis index map: image point i lies at node coordinate num/den with
 // num = (2i+1)(my-1), den = 2m; j0 = num div den, w1 = r/den, w0 = (den-r)/den
 // (float64 quotient, correctly rounded, then rounded to float32).
-__global__ void k_index_map(int32_t* j0, float* w0, float* w1, int m, int my) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ inline void index_map_entry(int32_t* j0, float* w0, float* w1, int m, int my, int i) {
     if (i >= m) return;
     const int64_t num = static_cast<int64_t>(2 * i + 1) * (my - 1);
     const int64_t den = 2 * static_cast<int64_t>(m);
@@ -53,6 +53,17 @@ __global__ void k_index_map(int32_t* j0, float* w0, float* w1, int m, int my) {
     j0[i] = static_cast<int32_t>(j);
     w1[i] = static_cast<float>(static_cast<double>(r) / static_cast<double>(den));
     w0[i] = static_cast<float>(static_cast<double>(den - r) / static_cast<double>(den));
+}
+
+__global__ void k_index_map(int32_t* j0, float* w0, float* w1, int m, int my) {
+    index_map_entry(j0, w0, w1, m, my, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// every axis (y) of every level (z) of a pyramid
+__global__ void k_index_maps(PyramidMaps a) {
+    const int d = blockIdx.y, l = blockIdx.z;
+    index_map_entry(a.j0[l][d], a.w0[l][d], a.w1[l][d], a.m[l][d], a.my[l][d],
+                    blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ __launch_bounds__(kThreads) void k_identity(float* y, int nx, int ny, int nz,
@@ -104,14 +115,35 @@ __global__ __launch_bounds__(kThreads) void k_prolongate(const float* __restrict
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_check_finite(const float* __restrict__ v,
-                                                           int64_t n, int* flag) {
-    int bad = 0;
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        bad |= !isfinite(v[i]);
+// Level 0 of a pyramid: R and T (blockIdx.y) copied, unless they are in place,
+// and checked on the way; *bad (pinned host memory, 0 before) becomes 1 if a
+// value is not finite.  Bound by the copy's traffic, which a copy and a check of
+// its own moved one and a half times: 256^3 44 us for both images, 149 + 41.
+__global__ __launch_bounds__(kThreads) void k_take_images(ImagePair p, int64_t n, int* bad) {
+    const float* src = p.src[blockIdx.y];
+    float* dst = p.dst[blockIdx.y];
+    const bool copy = src != dst;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kThreads;
+    const int64_t first = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
+    int off = 0;
+    int64_t done = 0;
+    if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0) {
+        const int64_t n4 = n >> 2;
+#pragma unroll 4
+        for (int64_t i = first; i < n4; i += step) {
+            const float4 v = reinterpret_cast<const float4*>(src)[i];
+            off |= !(isfinite(v.x) && isfinite(v.y) && isfinite(v.z) && isfinite(v.w));
+            if (copy) reinterpret_cast<float4*>(dst)[i] = v;
+        }
+        done = 4 * n4;
     }
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+#pragma unroll 4
+    for (int64_t i = done + first; i < n; i += step) {
+        const float v = src[i];
+        off |= !isfinite(v);
+        if (copy) dst[i] = v;
+    }
+    if (__any(off) && (threadIdx.x & 63) == 0) *bad = 1;
 }
 
 __global__ __launch_bounds__(kThreads) void k_fill(float* p, int64_t n, float v) {
@@ -134,10 +166,15 @@ __global__ __launch_bounds__(kThreads) void k_reduce_batch(const ReduceArgs* arg
 
 }  // namespace
 
-void launch_downsample(const float* src, float* dst, int mx, int my, int mz, hipStream_t s) {
+void launch_downsample(const ImagePair& p, int mx, int my, int mz, hipStream_t s) {
     const int64_t n = static_cast<int64_t>(mx / 2) * (my / 2) * (mz / 2);
-    hipLaunchKernelGGL(k_downsample, dim3(grid_for(n)), dim3(kThreads), 0, s, src, dst, mx, my,
-                       mz);
+    hipLaunchKernelGGL(k_downsample, dim3(grid_for(n), 2), dim3(kThreads), 0, s, p, mx, my, mz);
+}
+
+void launch_index_maps(const PyramidMaps& a, int levels, hipStream_t s) {
+    int m = 1;
+    for (int d = 0; d < 3; ++d) m = a.m[0][d] > m ? a.m[0][d] : m;
+    hipLaunchKernelGGL(k_index_maps, dim3((m + 255) / 256, 3, levels), dim3(256), 0, s, a);
 }
 
 void launch_index_map(int32_t* j0, float* w0, float* w1, int m, int my, hipStream_t s) {
@@ -157,9 +194,9 @@ void launch_prolongate(const float* yc, float* yf, int cx, int cy, int cz, hipSt
                        cz);
 }
 
-void launch_check_finite(const float* v, int64_t n, int* flag, hipStream_t s) {
-    hipLaunchKernelGGL(k_check_finite, dim3(grid_for(n, kThreads, 4096)), dim3(kThreads), 0, s,
-                       v, n, flag);
+void launch_take_images(const ImagePair& p, int64_t n, int* bad, hipStream_t s) {
+    hipLaunchKernelGGL(k_take_images, dim3(grid_for((n + 3) / 4, kThreads, 2048), 2),
+                       dim3(kThreads), 0, s, p, n, bad);
 }
 
 void launch_fill(float* p, int64_t n, float v, hipStream_t s) {

@@ -582,6 +582,20 @@ size_t diff_floats(const Level& L) {
     return static_cast<size_t>(part_floats(L, sens_variant(L)) + L.N());
 }
 
+// The reference side of the NGF term of a level, which only the general pass
+// reads: formed when that pass is chosen (256^3: 100 us of a registration).
+void form_rn(ngf_ctx* c, Level& L) {
+    launch_rn(L.R, L.rn, L.m[0], L.m[1], L.m[2], L.h[0], L.h[1], L.h[2], c->p.rho, c->stream);
+}
+void need_rn(ngf_ctx* c, Level& L) {
+    if (L.rn_ok) return;
+    form_rn(c, L);
+    // under capture the launch is part of the graph and has not run yet
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    L.rn_ok = cap == hipStreamCaptureStatusNone;
+}
+
 // Pick the image-pass variant of every level: forced, cached for this shape,
 // or the fastest of all variants over three timed evaluations at the identity
 // (whole evaluation: image pass, node pass and reduction).  The size rule's
@@ -590,15 +604,16 @@ size_t diff_floats(const Level& L) {
 // tell apart, and two contexts should not differ by the noise of a timing.
 constexpr float kTuneMargin = 0.06f;
 ngf_status autotune(ngf_ctx* c) {
-    if (c->forced_variant >= 0) {
+    if (c->forced_variant >= 0 || c->forced_variant == kVariantBySize) {
         // a variant that needs a ratio of 2 or 4 gives way to the general
         // pass on levels with other grids
-        for (Level& L : c->lv)
-            L.variant = variant_ok(L, c->forced_variant) ? c->forced_variant : kMarchGen;
-        return NGF_OK;
-    }
-    if (c->forced_variant == kVariantBySize) {
-        for (Level& L : c->lv) L.variant = variant_by_size(L);
+        for (Level& L : c->lv) {
+            L.variant = c->forced_variant == kVariantBySize ? variant_by_size(L)
+                        : variant_ok(L, c->forced_variant)  ? c->forced_variant
+                                                            : kMarchGen;
+            if (is_gen(L.variant)) need_rn(c, L);
+        }
+        HIPCHK(c, hipGetLastError());
         return NGF_OK;
     }
     if (!c->tune_loaded) {
@@ -618,6 +633,7 @@ ngf_status autotune(ngf_ctx* c) {
             if (kv.first == key) found = kv.second;
         if (found >= 0) {
             L.variant = found;
+            if (is_gen(found)) need_rn(c, L);
             continue;
         }
         launch_identity(c->ltmp, L.my[0], L.my[1], L.my[2], L.hy[0], L.hy[1], L.hy[2],
@@ -628,6 +644,7 @@ ngf_status autotune(ngf_ctx* c) {
         for (int v = 0; v < kNumVariants && st == NGF_OK; ++v) {
             if (!variant_ok(L, v)) continue;
             L.variant = v;
+            if (is_gen(v)) need_rn(c, L);
             st = enqueue_eval(c, L, L.R, L.T, c->ltmp, c->lgt);
             if (st != NGF_OK) break;
             if (hipEventRecord(e0, c->stream) != hipSuccess) st = NGF_E_HIP;
@@ -653,6 +670,111 @@ ngf_status autotune(ngf_ctx* c) {
     (void)hipEventDestroy(e1);
     c->prof = prof;
     return st;
+}
+
+ngf_status pyramid_enqueue(ngf_ctx* c, const float* R, const float* T, const ngf_grid* g,
+                           int32_t host_ptrs) {
+    if (!R || !T || !g) return fail(c, NGF_E_ARG, "null R, T or grid");
+    const int L = c->p.levels, r = c->p.ratio;
+    int64_t N = 1;
+    int n0[3];  // level-0 deformation-grid nodes per axis
+    for (int d = 0; d < 3; ++d) {
+        if (!(std::isfinite(g->h[d]) && g->h[d] > 0.0))
+            return fail(c, NGF_E_ARG, "spacing must be positive");
+        if (g->m[d] <= 0 || g->m[d] > 32768 || g->m[d] % (1 << (L - 1)) != 0)
+            return fail(c, NGF_E_SHAPE,
+                        "each m_d must be at most 32768 and divisible by 2^(levels-1)");
+        if (c->node_grid[d] == 0 && g->m[d] % (r << (L - 1)) != 0)
+            return fail(c, NGF_E_SHAPE, "each m_d must be divisible by ratio * 2^(levels-1)");
+        n0[d] = c->node_grid[d] ? c->node_grid[d] : g->m[d] / r + 1;
+        if ((n0[d] - 1) % (1 << (L - 1)) != 0)
+            return fail(c, NGF_E_SHAPE,
+                        "node cells m^y_d - 1 must be divisible by 2^(levels-1)");
+        const int mc = g->m[d] >> (L - 1), nc = ((n0[d] - 1) >> (L - 1)) + 1;
+        if (mc < 4 || nc < 3)
+            return fail(c, NGF_E_SHAPE, "coarsest level needs >= 4 cells and >= 2 node cells");
+        if (2 * (n0[d] - 1) > g->m[d])
+            return fail(c, NGF_E_SHAPE,
+                        "at least 2 image cells per deformation cell: 2 (m^y_d - 1) <= m_d");
+        // the image tiles (32 points in y and z) must each meet every index
+        // set of Eq. 3 in at most two tiles per axis
+        if (g->m[d] > 16 * (n0[d] - 1))
+            return fail(c, NGF_E_SHAPE,
+                        "at most 16 image cells per deformation cell: m_d <= 16 (m^y_d - 1)");
+        N *= g->m[d];
+    }
+    if (N >= (static_cast<int64_t>(1) << 30))
+        return fail(c, NGF_E_SHAPE, "image too large (at most 2^30 - 1 voxels)");
+    c->lb_level = -1;
+    c->lv.assign(L, Level{});
+    for (int l = 0; l < L; ++l) {
+        Level& lv = c->lv[l];
+        for (int d = 0; d < 3; ++d) {
+            lv.m[d] = g->m[d] >> l;
+            lv.h[d] = g->h[d] * static_cast<double>(1 << l);
+            lv.my[d] = ((n0[d] - 1) >> l) + 1;
+            lv.hy[d] = lv.m[d] * lv.h[d] / (lv.my[d] - 1);
+        }
+        lv.dyadic = 0;
+        for (const int q : {2, 4}) {
+            bool all = true;
+            for (int d = 0; d < 3; ++d) all = all && lv.m[d] % q == 0 && lv.my[d] == lv.m[d] / q + 1;
+            if (all) lv.dyadic = q;
+        }
+        const ngf_status e = bind_level_storage(c, l);
+        if (e != NGF_OK) {
+            c->lv.clear();
+            return e;
+        }
+    }
+    if (const ngf_status st = ensure_scratch(c, c->lv[0]); st != NGF_OK) return st;
+    if (ensure_lbfgs(c, static_cast<size_t>(3 * c->lv[0].Ny())) != NGF_OK) return NGF_E_OOM;
+
+    // Level 0 copied and checked, then the successive 2x2x2 means, both images a
+    // launch.  Images in host memory come on two side streams.
+    Level& F = c->lv[0];
+    ImagePair p{{R, T}, {F.R, F.T}};
+    if (host_ptrs) {
+        HIPCHK(c, hipEventRecord(c->join[0], c->stream));
+        for (int k = 0; k < 2; ++k) {
+            HIPCHK(c, hipStreamWaitEvent(c->side[k], c->join[0], 0));
+            HIPCHK(c, hipMemcpyAsync(p.dst[k], p.src[k], static_cast<size_t>(F.N()) * sizeof(float),
+                                     hipMemcpyHostToDevice, c->side[k]));
+            HIPCHK(c, hipEventRecord(c->join[1 + k], c->side[k]));
+        }
+    }
+    PyramidMaps maps{};
+    for (int l = 0; l < L; ++l)
+        for (int d = 0; d < 3; ++d) {
+            const Level& lv = c->lv[l];
+            maps.j0[l][d] = lv.j0[d];
+            maps.w0[l][d] = lv.w0[d];
+            maps.w1[l][d] = lv.w1[d];
+            maps.m[l][d] = lv.m[d];
+            maps.my[l][d] = lv.my[d];
+        }
+    launch_index_maps(maps, L, c->stream);
+    if (host_ptrs)
+        for (int k = 0; k < 2; ++k) {
+            HIPCHK(c, hipStreamWaitEvent(c->stream, c->join[1 + k], 0));
+            p.src[k] = p.dst[k];
+        }
+    *c->host_bad = 0;  // the last build that could set it has been waited for
+    launch_take_images(p, F.N(), c->host_bad, c->stream);
+    for (int l = 1; l < L; ++l) {
+        const Level &a = c->lv[l - 1], &b = c->lv[l];
+        launch_downsample(ImagePair{{a.R, a.T}, {b.R, b.T}}, a.m[0], a.m[1], a.m[2], c->stream);
+    }
+    HIPCHK(c, hipGetLastError());
+    return NGF_OK;
+}
+
+ngf_status pyramid_finish(ngf_ctx* c) {
+    if (*c->host_bad) {
+        c->lv.clear();
+        return fail(c, NGF_E_NONFINITE, "R or T holds NaN or infinity");
+    }
+    return autotune(c);
 }
 
 bool early_stop_met(double J_old, double J_new, double tol) {
@@ -909,9 +1031,12 @@ ngf_status ngf_create(const ngf_params* p, void* stream, ngf_ctx** out) {
     for (int i = 0; i < 3; ++i) chk(hipEventCreateWithFlags(&c->join[i], hipEventDisableTiming));
     chk(hipMalloc(reinterpret_cast<void**>(&c->jds), 8 * sizeof(double)));
     chk(hipHostMalloc(reinterpret_cast<void**>(&c->host_jds),
-                      8 * sizeof(double) + sizeof(LbCtl), hipHostMallocDefault));
+                      8 * sizeof(double) + sizeof(LbCtl) + sizeof(double), hipHostMallocDefault));
+    static_assert(sizeof(LbCtl) % sizeof(double) == 0, "the flag behind it is aligned");
+    if (s == NGF_OK)
+        c->host_bad = reinterpret_cast<int*>(reinterpret_cast<char*>(c->host_jds + 8) +
+                                             sizeof(LbCtl));
     chk(hipMalloc(reinterpret_cast<void**>(&c->st), sizeof(LbState)));
-    chk(hipMalloc(reinterpret_cast<void**>(&c->dflag), sizeof(int)));
     if (s == NGF_OK) s = static_scratch_setup(c);
     if (s != NGF_OK) {
         ngf_destroy(c);
@@ -937,7 +1062,7 @@ void ngf_destroy(ngf_ctx* c) {
     log_free(c);
     for (void* p : {static_cast<void*>(c->part), static_cast<void*>(c->dpart),
                     static_cast<void*>(c->spart), static_cast<void*>(c->gpart),
-                    static_cast<void*>(c->jds), static_cast<void*>(c->dflag),
+                    static_cast<void*>(c->jds),
                     static_cast<void*>(c->ly), static_cast<void*>(c->lg),
                     static_cast<void*>(c->lyt), static_cast<void*>(c->lgt),
                     static_cast<void*>(c->ld), static_cast<void*>(c->ltmp),
@@ -960,9 +1085,8 @@ ngf_status ngf_set_params(ngf_ctx* c, const ngf_params* p) {
     const bool rho_changed = p->rho != c->p.rho;
     c->p = *p;
     if (rho_changed) {
-        for (const Level& L : c->lv)
-            launch_rn(L.R, L.rn, L.m[0], L.m[1], L.m[2], L.h[0], L.h[1], L.h[2], c->p.rho,
-                      c->stream);
+        for (Level& L : c->lv)
+            if (L.rn_ok) form_rn(c, L);
         HIPCHK(c, hipGetLastError());
     }
     return NGF_OK;
@@ -972,108 +1096,9 @@ ngf_status ngf_build_pyramid(ngf_ctx* c, const float* R, const float* T, const n
                              int32_t host_ptrs) {
     if (!c) return NGF_E_ARG;
     const TraceRange range("ngf_build_pyramid");
-    if (!R || !T || !g) return fail(c, NGF_E_ARG, "null R, T or grid");
-    const int L = c->p.levels, r = c->p.ratio;
-    int64_t N = 1;
-    int n0[3];  // level-0 deformation-grid nodes per axis
-    for (int d = 0; d < 3; ++d) {
-        if (!(std::isfinite(g->h[d]) && g->h[d] > 0.0))
-            return fail(c, NGF_E_ARG, "spacing must be positive");
-        if (g->m[d] <= 0 || g->m[d] > 32768 || g->m[d] % (1 << (L - 1)) != 0)
-            return fail(c, NGF_E_SHAPE,
-                        "each m_d must be at most 32768 and divisible by 2^(levels-1)");
-        if (c->node_grid[d] == 0 && g->m[d] % (r << (L - 1)) != 0)
-            return fail(c, NGF_E_SHAPE, "each m_d must be divisible by ratio * 2^(levels-1)");
-        n0[d] = c->node_grid[d] ? c->node_grid[d] : g->m[d] / r + 1;
-        if ((n0[d] - 1) % (1 << (L - 1)) != 0)
-            return fail(c, NGF_E_SHAPE,
-                        "node cells m^y_d - 1 must be divisible by 2^(levels-1)");
-        const int mc = g->m[d] >> (L - 1), nc = ((n0[d] - 1) >> (L - 1)) + 1;
-        if (mc < 4 || nc < 3)
-            return fail(c, NGF_E_SHAPE, "coarsest level needs >= 4 cells and >= 2 node cells");
-        if (2 * (n0[d] - 1) > g->m[d])
-            return fail(c, NGF_E_SHAPE,
-                        "at least 2 image cells per deformation cell: 2 (m^y_d - 1) <= m_d");
-        // the image tiles (32 points in y and z) must each meet every index
-        // set of Eq. 3 in at most two tiles per axis
-        if (g->m[d] > 16 * (n0[d] - 1))
-            return fail(c, NGF_E_SHAPE,
-                        "at most 16 image cells per deformation cell: m_d <= 16 (m^y_d - 1)");
-        N *= g->m[d];
-    }
-    if (N >= (static_cast<int64_t>(1) << 30))
-        return fail(c, NGF_E_SHAPE, "image too large (at most 2^30 - 1 voxels)");
-    c->lb_level = -1;
-    c->lv.assign(L, Level{});
-    for (int l = 0; l < L; ++l) {
-        Level& lv = c->lv[l];
-        for (int d = 0; d < 3; ++d) {
-            lv.m[d] = g->m[d] >> l;
-            lv.h[d] = g->h[d] * static_cast<double>(1 << l);
-            lv.my[d] = ((n0[d] - 1) >> l) + 1;
-            lv.hy[d] = lv.m[d] * lv.h[d] / (lv.my[d] - 1);
-        }
-        lv.dyadic = 0;
-        for (const int q : {2, 4}) {
-            bool all = true;
-            for (int d = 0; d < 3; ++d) all = all && lv.m[d] % q == 0 && lv.my[d] == lv.m[d] / q + 1;
-            if (all) lv.dyadic = q;
-        }
-        const ngf_status e = bind_level_storage(c, l);
-        if (e != NGF_OK) {
-            c->lv.clear();
-            return e;
-        }
-    }
-    if (const ngf_status st = ensure_scratch(c, c->lv[0]); st != NGF_OK) return st;
-    if (ensure_lbfgs(c, static_cast<size_t>(3 * c->lv[0].Ny())) != NGF_OK) return NGF_E_OOM;
-
-    // R on side stream 0, T on side stream 1, each: copy level 0, then the
-    // successive 2x2x2 means; both join the context stream.
-    const size_t bytes0 = static_cast<size_t>(c->lv[0].N()) * sizeof(float);
-    HIPCHK(c, hipEventRecord(c->join[0], c->stream));
-    for (int k = 0; k < 2; ++k) {
-        hipStream_t s = c->side[k];
-        HIPCHK(c, hipStreamWaitEvent(s, c->join[0], 0));
-        const float* src = k == 0 ? R : T;
-        float* dst0 = k == 0 ? c->lv[0].R : c->lv[0].T;
-        HIPCHK(c, hipMemcpyAsync(dst0, src, bytes0,
-                                 host_ptrs ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, s));
-        for (int l = 1; l < L; ++l) {
-            const Level& a = c->lv[l - 1];
-            float* out = k == 0 ? c->lv[l].R : c->lv[l].T;
-            launch_downsample(k == 0 ? a.R : a.T, out, a.m[0], a.m[1], a.m[2], s);
-        }
-        HIPCHK(c, hipGetLastError());
-        HIPCHK(c, hipEventRecord(c->join[1 + k], s));
-    }
-    for (int l = 0; l < L; ++l)
-        for (int d = 0; d < 3; ++d)
-            launch_index_map(c->lv[l].j0[d], c->lv[l].w0[d], c->lv[l].w1[d], c->lv[l].m[d],
-                             c->lv[l].my[d], c->stream);
-    HIPCHK(c, hipStreamWaitEvent(c->stream, c->join[1], 0));
-    HIPCHK(c, hipStreamWaitEvent(c->stream, c->join[2], 0));
-    // reference side of the NGF term, per level (general image pass)
-    for (int l = 0; l < L; ++l) {
-        const Level& lv = c->lv[l];
-        launch_rn(lv.R, lv.rn, lv.m[0], lv.m[1], lv.m[2], lv.h[0], lv.h[1], lv.h[2], c->p.rho,
-                  c->stream);
-    }
-    HIPCHK(c, hipGetLastError());
-    // reject non-finite inputs
-    int zero = 0;
-    HIPCHK(c, hipMemcpyAsync(c->dflag, &zero, sizeof(int), hipMemcpyHostToDevice, c->stream));
-    launch_check_finite(c->lv[0].R, c->lv[0].N(), c->dflag, c->stream);
-    launch_check_finite(c->lv[0].T, c->lv[0].N(), c->dflag, c->stream);
-    int bad = 0;
-    HIPCHK(c, hipMemcpyAsync(&bad, c->dflag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    if (const ngf_status e = pyramid_enqueue(c, R, T, g, host_ptrs); e != NGF_OK) return e;
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (bad) {
-        c->lv.clear();
-        return fail(c, NGF_E_NONFINITE, "R or T holds NaN or infinity");
-    }
-    const ngf_status ts = autotune(c);
-    if (ts != NGF_OK) return ts;
+    if (const ngf_status e = pyramid_finish(c); e != NGF_OK) return e;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return NGF_OK;
 }
@@ -1332,14 +1357,15 @@ ngf_status ngf_register_levels(ngf_ctx* c, float* y_out, ngf_report* rep) {
         const auto t_level = std::chrono::steady_clock::now();
         const Level& lv = c->lv[lev];
         if (lev == L - 1) {
-            launch_identity(c->ltmp, lv.my[0], lv.my[1], lv.my[2], lv.hy[0], lv.hy[1], lv.hy[2],
+            launch_identity(c->ly, lv.my[0], lv.my[1], lv.my[2], lv.hy[0], lv.hy[1], lv.hy[2],
                             c->stream);
         } else {
             const Level& C = c->lv[lev + 1];
             launch_prolongate(c->ly, c->ltmp, C.my[0], C.my[1], C.my[2], c->stream);
+            std::swap(c->ly, c->ltmp);
         }
         HIPCHK(c, hipGetLastError());
-        ngf_status e = ngf_lbfgs_reset(c, lev, c->ltmp);
+        ngf_status e = ngf_lbfgs_reset(c, lev, c->ly);
         if (e != NGF_OK) return e;
         int it = 0;
         int32_t info = NGF_INFO_MAX_ITER;

@@ -123,14 +123,25 @@ ngf_status build_pairs(ngf_batch* b, int np, const float* const* R, const float*
         b->pctx.push_back(c);
     }
     const int var = graph_variant(b);
-    for (int i = 0; i < np; ++i) {
-        ngf_ctx* c = b->pctx[i];
+    // everything queued first, then one wait for all pairs
+    ngf_status st = NGF_OK;
+    int queued = 0;
+    for (; queued < np && st == NGF_OK; ++queued) {
+        ngf_ctx* c = b->pctx[queued];
         c->p = b->p;
-        if (ngf_set_kernel(c, var) != NGF_OK) return bfail(b, NGF_E_ARG, c->err);
-        // the shared timed-selection table: in before the pyramid, out after
-        c->tune_loaded = true;
-        c->tune_cache = b->tune;
-        const ngf_status s = ngf_build_pyramid(c, R[i], T[i], &grids[i], 0);
+        c->forced_variant = var;
+        st = pyramid_enqueue(c, R[queued], T[queued], &grids[queued], 0);
+    }
+    if (hipStreamSynchronize(b->stream) != hipSuccess) return bfail(b, NGF_E_HIP, "sync");
+    for (int i = 0; i < queued; ++i) {
+        ngf_ctx* c = b->pctx[i];
+        ngf_status s = i == queued - 1 ? st : NGF_OK;  // the failure that ended the queueing
+        if (s == NGF_OK) {
+            // the shared timed-selection table: in before the choice, out after
+            c->tune_loaded = true;
+            c->tune_cache = b->tune;
+            s = pyramid_finish(c);
+        }
         if (s != NGF_OK) return bfail(b, s, "pair " + std::to_string(i) + ": " + c->err);
         b->tune = c->tune_cache;
     }
@@ -233,16 +244,14 @@ ngf_status graph_register(ngf_batch* b, int np, const float* const* R, const flo
             // start point: identity on the coarsest level, else the prolongated
             // result of the coarser level
             if (lev == L - 1) {
-                launch_identity(c->ltmp, lv.my[0], lv.my[1], lv.my[2], lv.hy[0], lv.hy[1],
+                launch_identity(c->ly, lv.my[0], lv.my[1], lv.my[2], lv.hy[0], lv.hy[1],
                                 lv.hy[2], s);
             } else {
                 const Level& C = c->lv[lev + 1];
                 launch_prolongate(c->ly, c->ltmp, C.my[0], C.my[1], C.my[2], s);
+                std::swap(c->ly, c->ltmp);
             }
             const int64_t n = 3 * lv.Ny();
-            if (hipMemcpyAsync(c->ly, c->ltmp, n * sizeof(float), hipMemcpyDeviceToDevice, s) !=
-                hipSuccess)
-                return bfail(b, NGF_E_HIP, "hipMemcpyAsync of a start point failed");
             c->lb_level = lev;
             const EvalArgs e0 = eval_args(c, lv, lv.R, lv.T, c->ly, c->lg, nullptr, nullptr);
             const EvalArgs e1 =

@@ -28,6 +28,7 @@ struct Level {
     float* w0[3] = {nullptr, nullptr, nullptr};
     float* w1[3] = {nullptr, nullptr, nullptr};
     float4* rn = nullptr;   // reference side of the NGF term (general image pass)
+    bool rn_ok = false;     // rn holds it (formed once the general pass is chosen)
     int variant = kTile3D;  // image-pass variant (autotuned or forced)
     // every axis has m^y = m/r + 1 for one r in {2, 4}: 2 or 4; otherwise 0
     // (then only the general image pass applies)
@@ -78,7 +79,7 @@ struct ngf_ctx {
     size_t nblk_cap = 0;
     double* jds = nullptr;       // device {J, D, S, max|g|, |g|^2, ...}
     double* host_jds = nullptr;  // pinned: 8 doubles, then room for an LbCtl
-    int* dflag = nullptr;
+    int* host_bad = nullptr;     // pinned, behind host_jds: a build met a non-finite input
 
     // L-BFGS
     size_t lb_cap = 0;  // floats per vector
@@ -146,6 +147,11 @@ struct Geo {
 Geo geometry(const Level& L, int variant);
 int tiles(int m, int t);
 int64_t node_blocks(const Level& L);
+// ngf_build_pyramid in two parts: everything queued on the context's stream, and
+// (after a synchronisation) the check of the inputs and the choice of variants.
+ngf_status pyramid_enqueue(ngf_ctx* c, const float* R, const float* T, const ngf_grid* g,
+                           int32_t host_ptrs);
+ngf_status pyramid_finish(ngf_ctx* c);
 // Image-pass variant of a level from the voxels that a launch covers.
 int variant_for(const Level& L, int64_t voxels);
 // Chooses the x chunks of levels in one launch of a fitted marching variant.

@@ -349,7 +349,20 @@ void launch_lb_accept_batch(const LbVecArgs* args, const BlockRef* blk, int nblk
 void launch_ctl_gather(const LbVecArgs* args, LbCtl* out, int npairs, hipStream_t s);
 
 // kernels (definitions in the .hip files), launched from the host code
-void launch_downsample(const float* src, float* dst, int mx, int my, int mz, hipStream_t s);
+// R and T, and where they go
+struct ImagePair {
+    const float* src[2];
+    float* dst[2];
+};
+// the index maps of a pyramid, per level and axis
+struct PyramidMaps {
+    int32_t* j0[NGF_MAX_LEVELS][3];
+    float* w0[NGF_MAX_LEVELS][3];
+    float* w1[NGF_MAX_LEVELS][3];
+    int m[NGF_MAX_LEVELS][3], my[NGF_MAX_LEVELS][3];
+};
+void launch_downsample(const ImagePair& p, int mx, int my, int mz, hipStream_t s);
+void launch_index_maps(const PyramidMaps& a, int levels, hipStream_t s);
 void launch_index_map(int32_t* j0, float* w0, float* w1, int m, int my, hipStream_t s);
 void launch_identity(float* y, int nx, int ny, int nz, double hx, double hy, double hz,
                      hipStream_t s);
@@ -371,7 +384,7 @@ void launch_rn(const float* R, float4* rn, int mx, int my, int mz, double hx, do
                double hz, double rho, hipStream_t s);
 void launch_node_pass(const NodePassArgs& a, hipStream_t s);
 void launch_reduce(const ReduceArgs& a, hipStream_t s);
-void launch_check_finite(const float* v, int64_t n, int* flag, hipStream_t s);
+void launch_take_images(const ImagePair& p, int64_t n, int* bad, hipStream_t s);
 void launch_fill(float* p, int64_t n, float v, hipStream_t s);
 void launch_image_pass_atomic(const ImagePassArgs& a, int ratio, int variant, hipStream_t s);
 

@@ -1,0 +1,110 @@
+"""The pyramid build's own paths: images in host and in device memory, at
+addresses with and without 16-byte alignment, sizes with and without a
+remainder, and a non-finite value at every place a thread can miss.  The images
+are copies and exact float64 means: compared bit for bit."""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _at(t, offset):
+    """A contiguous copy of t that starts `offset` floats into its storage."""
+    import torch
+    buf = torch.empty(t.numel() + offset, device=t.device)
+    v = buf[offset:].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+def _mean(t):
+    v = t.double()
+    v = v[..., 0::2] + v[..., 1::2]
+    v = v[:, 0::2] + v[:, 1::2]
+    return ((v[0::2] + v[1::2]) * 0.125).float()
+
+
+@pytest.mark.parametrize("m,levels", [((8, 8, 8), 2), ((10, 6, 14), 1), ((40, 72, 88), 3)])
+@pytest.mark.parametrize("where", ["device", "offset", "host"])
+def test_images(gpu_lib, m, levels, where):
+    import torch
+    ngf = gpu_lib
+    print(f"[build] m={m} levels={levels} {where}", flush=True)
+    gen = torch.Generator().manual_seed(3)
+    R, T = (100.0 * torch.randn(m, generator=gen) for _ in range(2))
+    if where != "host":
+        R, T = R.cuda(), T.cuda()
+    if where == "offset":
+        R, T = _at(R, 1), _at(T, 3)
+    with ngf.Context(alpha=0.1, tau=1.0, rho=1.0, levels=levels) as ctx:
+        ctx.set_kernel("by_size")
+        for _ in range(2):  # and again into the same storage
+            ctx.build_pyramid(R, T)
+            for lev in range(levels):
+                a, b = ctx.level_images(lev)
+                r, t = R.cuda(), T.cuda()
+                for _ in range(lev):
+                    r, t = _mean(r), _mean(t)
+                assert torch.equal(a, r) and torch.equal(b, t), lev
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("m,nodes", [((6, 10, 14), None), ((5, 7, 9), (3, 3, 4))])
+def test_non_finite_values(gpu_lib, m, nodes, offset):
+    import torch
+    ngf = gpu_lib
+    good = torch.randn(m, device="cuda")
+    with ngf.Context(alpha=0.1, tau=1.0, rho=1.0, levels=1) as ctx:
+        ctx.set_kernel("by_size")
+        if nodes is not None:
+            ctx.set_node_grid(nodes)
+        for where in (0, 1, good.numel() // 2, good.numel() - 2, good.numel() - 1):
+            for value in (float("nan"), float("inf"), float("-inf")):
+                bad = good.clone()
+                bad.view(-1)[where] = value
+                for pair in ((bad, good), (good, bad)):
+                    print(f"[build] value {value} at {where}", flush=True)
+                    with pytest.raises(ngf.NgfError) as e:
+                        ctx.build_pyramid(*(_at(p, offset) for p in pair))
+                    assert e.value.status == ngf.E_NONFINITE
+        ctx.build_pyramid(good, good)
+
+
+def test_batch_reports_the_first_pair_that_failed(gpu_lib):
+    import torch
+    ngf = gpu_lib
+    good = torch.randn((16, 16, 16), device="cuda")
+    nan = good.clone()
+    nan[2, 3, 4] = float("nan")
+    odd = torch.zeros((15, 16, 16), device="cuda")
+    b = ngf.Batch(alpha=0.1, tau=1.0, rho=1.0, levels=1, max_iter=2)
+    for Rs, Ts, status, pair in (([good, good, odd], [nan, good, odd], ngf.E_NONFINITE, 0),
+                                 ([good, odd, good], [good, odd, nan], ngf.E_SHAPE, 1),
+                                 ([good, good], [good, nan], ngf.E_NONFINITE, 1)):
+        with pytest.raises(ngf.NgfError) as e:
+            b.build(Rs, Ts)
+        assert e.value.status == status and f"pair {pair}" in str(e.value)
+    b.build([good], [good])
+    b.close()
+
+
+def test_general_pass_chosen_after_the_build(gpu_lib):
+    """The reference side that only the general pass reads is formed when that
+    pass is chosen, and again with a new rho."""
+    import torch
+    ngf = gpu_lib
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    R, T = (100.0 * torch.randn((32, 48, 40), device="cuda", generator=gen) for _ in range(2))
+    with ngf.Context(alpha=0.1, tau=10.0, rho=10.0, levels=2) as ctx:
+        ctx.set_kernel("by_size")
+        ctx.build_pyramid(R, T)
+        y = ctx.identity(1)
+        y += 0.3
+        for rho in (10.0, 25.0):
+            ctx.set_params(rho=rho)
+            ctx.set_kernel("by_size")
+            J, g, _ = ctx.eval_J_grad(1, y)
+            ctx.set_kernel("general")
+            Jg, gg, _ = ctx.eval_J_grad(1, y)
+            assert abs(Jg - J) <= 1e-5 * abs(J)
+            assert float((gg - g).norm()) <= 1e-4 * float(g.norm())
