@@ -144,14 +144,6 @@ __device__ inline float uniform(float v) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-// Truncation to an integer, saturating, a NaN to 0 (a C++ cast leaves what does
-// not fit undefined).
-__device__ inline int to_int(double v) {
-    int i;
-    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(v));
-    return i;
-}
-
 // Fixes where v is computed: without it the compiler sinks what forms dT into
 // the stage that uses it two planes later and carries its many operands over.
 __device__ inline void settle(float& v) { asm volatile("" : "+v"(v)); }
@@ -182,21 +174,6 @@ __device__ inline float cell_sum_z(float v, float w0, float w1) {
         hi += dpp<0xB1>(hi);
         hi += dpp<0x4E>(hi);
         return (threadIdx.x & 1) ? hi : lo;
-    }
-}
-
-// Continuous template index along one axis, yh / h - 1/2.  A power-of-two
-// spacing has an exact reciprocal; any other takes the product with the
-// rounded one and a correction by the remainder, which makes the quotient
-// exact whenever it is representable and its error at most an ulp otherwise.
-template <bool POW2>
-__device__ inline double index_of(double yh, double h, double ih) {
-    if constexpr (POW2) {
-        return fma(yh, ih, -0.5);
-    } else {
-        const double a = fmin(fmax(yh, -1e300), 1e300);  // an infinity would make the remainder NaN
-        const double q = a * ih;
-        return fma(fma(-q, h, a), ih, q) - 0.5;
     }
 }
 

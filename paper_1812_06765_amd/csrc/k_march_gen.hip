@@ -28,7 +28,15 @@
 //     reduced along z and y onto the tile's nodes, one stage per step
 //     (write, z sums, y sums and store), in the slack of the following steps.
 // The reference side of the NGF term (grad R and 1/(|grad R|^2 + rho^2)) is
-// read from a per-level array prepared once per pyramid (k_rn).
+// read from a per-level array formed when this pass is chosen (k_rn).
+//
+// One workgroup of 16 waves a CU, so what a step waits for or repeats in every
+// wave is not hidden: the reference side is in flight over W; the index maps
+// along x of 64 planes are held a plane a lane and read by lane; dT and the
+// fractions are settled where they are formed, which keeps 121 registers from
+// spilling; cell and fraction come from one conversion and a median.
+// 191 x 203 x 157 on 64 x 68 x 53 nodes: evaluation 146 -> 128 us (spacings that
+// need a division 152 -> 132), J alone 95 -> 86.
 #include "ngf_internal.h"
 
 #include <math.h>
@@ -101,6 +109,18 @@ __device__ inline Map1 map1(int i, int m, int n) {
     return r;
 }
 __device__ inline int map_j0(int i, int m, int n) { return ((2 * i + 1) * (n - 1)) / (2 * m); }
+
+// Makes v a value formed here: the compiler otherwise sinks its whole formation
+// to the guarded use two planes later, with everything it is formed from.
+__device__ inline void settle(float& v) { asm volatile("" : "+v"(v)); }
+
+// v of a lane (uniform), as a scalar
+__device__ inline double lane_d(double v, int lane) {
+    const uint64_t b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(b), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(b >> 32), lane);
+    return __longlong_as_double(static_cast<uint64_t>(hi) << 32 | lo);
+}
 
 __device__ inline double wave_sum_d(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
@@ -248,8 +268,12 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
     };
     float qv0[GKQ], qv1[GKQ];
     double qwx0 = 1.0, qwx1 = 0.0;
-    auto load_q = [&](int p) {
-        const Map1 mp = map1(clampi(p, 0, mx - 1), mx, nx);
+    // index maps along x of 64 planes from x0 - 2 + (k & ~63) on, a plane a lane
+    Map1 xmap = {};
+    auto load_q = [&](int k) {  // of plane x0 - 2 + k
+        if ((k & 63) == 0) xmap = map1(clampi(x0 - 2 + k + (t & 63), 0, mx - 1), mx, nx);
+        const Map1 mp = {__builtin_amdgcn_readlane(xmap.j0, k & 63), lane_d(xmap.w0, k & 63),
+                         lane_d(xmap.w1, k & 63)};
         qwx0 = mp.w0;
         qwx1 = mp.w1;
 #pragma unroll
@@ -330,13 +354,27 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
             for (int kk = 0; kk < KP; ++kk) sG[c * GNI + t + kk * GNT] = acc[kk][c];
     };
 
-    load_q(x0 - 2);
+    load_q(0);
     store_q(0);
     __syncthreads();
 
     for (int k = 0; k < nstep; ++k) {
         const int slot = k & 1;
         const int pw = x0 - 2 + k;
+        // the reference side at plane pv, in flight over W
+        const int pv = pw - 1;
+        const bool vplane = pv >= max(x0 - 1, 0) && pv <= min(xend, mx - 1);
+        float4 rnv[NPOS];
+        if (vplane) {
+            const uint64_t rnb = static_cast<uint64_t>(pv) * static_cast<uint64_t>(sxT) * 16u;
+            const __amdgpu_buffer_rsrc_t rR =
+                rsrc(reinterpret_cast<const unsigned char*>(a.rn) + rnb,
+                     static_cast<uint32_t>(sxT) * 16u);
+#pragma unroll
+            for (int kk = 0; kk < NPOS; ++kk)
+                if (kk != RK || face)
+                    rnv[kk] = bld4(rR, static_cast<uint32_t>(gyof(kk) * mz + gzof(kk)) * 16u, 0u);
+        }
         // ------------- W: P and the warp of plane pw -----------------------
         {
             const double* Q = sQ + slot * 3 * GNQ;
@@ -360,12 +398,14 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
                 int i0[3];
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    const double xi = POW2 ? fma(yh[d], ih[d], -0.5) : yh[d] / hh[d] - 0.5;
-                    const double xc = fmin(fmax(xi, 0.0), static_cast<double>(mm[d] - 1));
-                    if (kk < KP) ss[kk < KP ? kk : 0][d] = xc == xi ? 1.0f : 0.0f;
-                    const int i = min(static_cast<int>(xc), mm[d] - 2);
+                    const double xi = index_of<POW2>(yh[d], hh[d], ih[d]);
+                    // the fraction leaves [0, 1] exactly where the index leaves the domain
+                    const int i = min(max(to_int(xi), 0), mm[d] - 2);
+                    const double r = xi - static_cast<double>(i);
+                    if (kk < KP) ss[kk < KP ? kk : 0][d] = r >= 0.0 && r <= 1.0 ? 1.0f : 0.0f;
                     i0[d] = i;
-                    ff[kk][d] = static_cast<float>(xc - static_cast<double>(i));
+                    ff[kk][d] = __builtin_amdgcn_fmed3f(static_cast<float>(r), 0.0f, 1.0f);
+                    settle(ff[kk][d]);
                 }
                 const uint32_t tb = static_cast<uint32_t>(i0[0] * sxT + i0[1] * mz + i0[2]) * 4u;
                 const uint32_t row4 = static_cast<uint32_t>(mz) * 4u;
@@ -381,7 +421,7 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
                 tv[kk][7] = t11.y;
             }
             // prefetch of the next Q plane's nodes (stored after V and E)
-            if (k + 1 < nstep) load_q(pw + 1);
+            if (k + 1 < nstep) load_q(k + 1);
             float* Ty = sTy + slot * GNH;
 #pragma unroll
             for (int kk = 0; kk < NPOS; ++kk) {
@@ -411,21 +451,18 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
                     dT[0][q][1] = fmaf(fx, d1, qx * d0) * (ss[q][1] * a.fihy);
                     const float ez0 = fmaf(fyv, e01, qy * e00), ez1 = fmaf(fyv, e11, qy * e10);
                     dT[0][q][2] = fmaf(fx, ez1, qx * ez0) * (ss[q][2] * a.fihz);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) settle(dT[0][q][c]);
                 }
             }
         }
         // ------------- V: NGF on plane pv = pw - 1 -------------------------
-        const int pv = pw - 1;
         float vxc[KP];
 #pragma unroll
         for (int kk = 0; kk < KP; ++kk) vxc[kk] = 0.0f;
-        if (pv >= max(x0 - 1, 0) && pv <= min(xend, mx - 1)) {
+        if (vplane) {
             const float* T0 = sTy + (slot ^ 1) * GNH;  // plane pv
             const bool dplane = pv >= x0 && pv < xend;
-            const uint64_t rnb = static_cast<uint64_t>(pv) * static_cast<uint64_t>(sxT) * 16u;
-            const __amdgpu_buffer_rsrc_t rR =
-                rsrc(reinterpret_cast<const unsigned char*>(a.rn) + rnb,
-                     static_cast<uint32_t>(sxT) * 16u);
             float* Vy = sVy + (pv & 1) * GVY;
             float* Vz = sVz + (pv & 1) * GVZ;
             const float tau = a.tau, rho = a.rho;
@@ -434,7 +471,7 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
                 if (kk == RK && !face) continue;
                 const int gy = gyof(kk), gz = gzof(kk);
                 const int p = (gy - y0 + 2) * GH + (gz - z0 + 2);  // the clamped voxel
-                const float4 rn = bld4(rR, static_cast<uint32_t>(gy * mz + gz) * 16u, 0u);
+                const float4 rn = rnv[kk];
                 const float gRx = rn.x, gRy = rn.y, gRz = rn.z, bb = rn.w;
                 const float ibb = __builtin_amdgcn_rcpf(bb);
                 const float gTx = (tyv[kk][2] - tyv[kk][0]) * a.i2hx;
@@ -497,8 +534,7 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
             if (pe >= x0 && pe < xend) {
                 const float* Vy = sVy + (pe & 1) * GVY;
                 const float* Vz = sVz + (pe & 1) * GVZ;
-                const Map1 mpx = map1(pe, mx, nx);
-                if (mpx.j0 > jA) {  // node plane jA is complete
+                if (a.j0x[pe] > jA) {  // node plane jA is complete
                     stage_w(accl);
                     pendZ = jA;
 #pragma unroll
@@ -510,7 +546,7 @@ __device__ __forceinline__ void gen_body(const ImagePassArgs& a, int CX, int blo
                         }
                     jA += 1;
                 }
-                const float wx0 = static_cast<float>(mpx.w0), wx1 = static_cast<float>(mpx.w1);
+                const float wx0 = a.w0x[pe], wx1 = a.w1x[pe];
 #pragma unroll
                 for (int kk = 0; kk < KP; ++kk) {
                     // v_x of planes pe - 1 and pe + 1; mirrored ghosts outside

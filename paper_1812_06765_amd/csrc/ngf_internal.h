@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/ngfreg.h"
+#include <math.h>
 #include <stdint.h>
 
 namespace ngf {
@@ -142,6 +143,29 @@ __host__ __device__ inline NodeTiles node_tiles(int j, int m, int n, int te) {
     r.tb = tb != r.ta ? tb : -1;
     r.lb = tb != r.ta ? j - map_lower(tb * te, m, n) : 0;
     return r;
+}
+
+// Truncation to an integer, saturating, a NaN to 0 (a C++ cast leaves what does
+// not fit undefined).
+__device__ inline int to_int(double v) {
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(v));
+    return i;
+}
+
+// Continuous template index along one axis, yh / h - 1/2.  A power-of-two
+// spacing has an exact reciprocal; any other takes the product with the
+// rounded one and a correction by the remainder, which makes the quotient
+// exact whenever it is representable and its error at most an ulp otherwise.
+template <bool POW2>
+__device__ inline double index_of(double yh, double h, double ih) {
+    if constexpr (POW2) {
+        return fma(yh, ih, -0.5);
+    } else {
+        const double a = fmin(fmax(yh, -1e300), 1e300);  // an infinity would make the remainder NaN
+        const double q = a * ih;
+        return fma(fma(-q, h, a), ih, q) - 0.5;
+    }
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own

@@ -81,3 +81,26 @@ def test_infinite_and_nan_positions(gpu_lib, variant):
                 with pytest.raises(ngf.NgfError) as e:
                     ctx.eval_J_grad(0, y)
                 assert e.value.status == ngf.E_NONFINITE
+
+
+@pytest.mark.parametrize("h", [(1.0, 1.0, 1.0), (0.9, 1.1, 1.3)])
+def test_general_pass_long_chunks(gpu_lib, h):
+    """The general pass with more than 64 planes a workgroup (its tables along x
+    hold 64), against the library's float64 evaluation."""
+    import torch
+    ngf = gpu_lib
+    m, nodes = (72, 500, 509), (30, 200, 211)  # 16 x 16 tiles: one chunk along x
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    R, T = (100.0 * torch.randn(m, device="cuda", generator=gen) for _ in range(2))
+    print(f"[general] m={m} nodes={nodes} h={h}", flush=True)
+    with ngf.Context(alpha=0.1, tau=10.0, rho=10.0, levels=1) as ctx:
+        ctx.set_node_grid(nodes)
+        ctx.set_kernel("by_size")
+        ctx.build_pyramid(R, T, h)
+        y = ctx.identity(0)
+        y += 0.4 * torch.randn(y.shape, device="cuda", generator=gen)
+        J, g, _ = ctx.eval_J_grad(0, y)
+        Jv, _, _ = ctx.eval_J_grad(0, y, want_grad=False)
+        J64, g64, _ = ctx.eval_J_grad_f64(0, y.double())
+    assert abs(J - J64) <= 1e-5 * abs(J64) and abs(Jv - J) <= 1e-12 * abs(J)
+    assert float((g.double() - g64).norm()) <= 1e-4 * float(g64.norm())
