@@ -559,9 +559,9 @@ void tune_cache_store(const std::string& key, int v) {
 // Image-pass variant from the level size alone, for callers that cannot
 // afford timing runs (or whose timings would be disturbed by concurrent
 // work).  Whole evaluations on gfx950, us, 3D tile of 4 x 4 x 16 / marching
-// over 16 x 32 / over 32 x 32: 32^3 21 / 34 / 37, 64 x 80 x 48 29 / 35 / 37,
-// 64^3 31 / 36 / 39, 90 x 106 x 74 58 / 40 / 46, 96^3 65 / 42 / 42, 128^3 130 /
-// 58 / 57, 256^3 892 / 208 / 204: a small level has too few marching
+// over 16 x 32 / over 32 x 32: 32^3 17 / 30 / 33, 64 x 80 x 48 26 / 31 / 34,
+// 64^3 25 / 31 / 34, 90 x 106 x 74 55 / 36 / 43, 96^3 59 / 36 / 37, 128^3 125 /
+// 53 / 52, 256^3 881 / 198 / 194: a small level has too few marching
 // workgroups to fill the device and is bound by their chain of planes, a
 // large one by the halo's work.
 int variant_for(const Level& L, int64_t voxels) {
