@@ -349,7 +349,8 @@ ngf_status ngf_register_levels(ngf_ctx* ctx, float* y_out, ngf_report* rep);
  *   grad_y     device float32 like y, or NULL; grad_T device float32 like T,
  *              or NULL; both NULL: only J is computed, with the plain
  *              evaluation's kernels (no scatter)
- * Allocates index maps and scratch on the first call for a new grid. */
+ * Allocates index maps and scratch on the first call for a new grid, and room
+ * for e on the first that asks for grad_T. */
 ngf_status ngf_eval_pair(ngf_ctx* ctx, const ngf_grid* g, const int32_t my[3],
                          const float* R, const float* T, const float* y,
                          const double* gscale, double* J, double* J_dev,

@@ -207,9 +207,8 @@ bool march_fits(const Level& P) {
     return ok;
 }
 
-// `floats`: at least so many of P^T partial sums
-ngf_status ensure_scratch(ngf_ctx* c, const Level& L, size_t floats = 0) {
-    size_t pf = floats, nt = 0;
+ngf_status ensure_scratch(ngf_ctx* c, const Level& L) {
+    size_t pf = 0, nt = 0;
     for (int v = 0; v < kNumVariants; ++v) {
         if (!variant_ok(L, v)) continue;
         pf = std::max(pf, static_cast<size_t>(part_floats(L, v)));
@@ -577,9 +576,27 @@ int sens_variant(const Level& L) {
     const int v = variant_by_size(L);
     return v == kTile3DTiny ? kMarch32Fit : v;
 }
-// Floats of its scratch: the partial sums, then e per voxel.
-size_t diff_floats(const Level& L) {
-    return static_cast<size_t>(part_floats(L, sens_variant(L)) + L.N());
+// Whether there is room for its e per voxel.  The buffer is its own: one that
+// cannot be had costs nothing but the form that stores e.  Under capture, where
+// nothing can be allocated, what an earlier call left has to do.
+bool sens_room(ngf_ctx* c, const Level& L) {
+    const size_t n = static_cast<size_t>(L.N());
+    if (n <= c->sens_cap) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone || (c->faults & NGF_FAULT_ALLOC)) return false;
+    // queued work may use the old buffer
+    if (c->sens && hipStreamSynchronize(c->stream) != hipSuccess) return false;
+    dfree(c->sens);
+    c->sens = nullptr;
+    c->sens_cap = 0;
+    if (hipMalloc(reinterpret_cast<void**>(&c->sens), n * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();
+        c->sens = nullptr;
+        return false;
+    }
+    c->sens_cap = n;
+    return true;
 }
 
 // The reference side of the NGF term of a level, which only the general pass
@@ -884,10 +901,10 @@ ngf_status finish_J(ngf_ctx* c, double* J) {
 
 // Differentiation form without the scatter of grad y: the evaluation's own
 // kernels (P^T as a gather), and grad_T from the sensitivities that the image
-// pass stores on the way, in the scratch behind the partial sums.  Forward and
-// backward of 128^3 with both gradients 282 -> 130 us; the scattering form
-// (eval_scatter) remains for callers whose scratch has no room for a value per
-// voxel, and for grids beyond the marching kernels' limits.
+// pass stores on the way (sens_room).  Forward and backward of 128^3 with both
+// gradients 282 -> 130 us; the scattering form (eval_scatter) remains for callers
+// who have no room for a value per voxel, and for grids beyond the marching
+// kernels' limits.
 ngf_status eval_diff(ngf_ctx* c, const Level& P, const float* R, const float* T, const float* y,
                      const double* gscale, double* J, double* J_dev, float* grad_y,
                      float* grad_T) {
@@ -899,7 +916,7 @@ ngf_status eval_diff(ngf_ctx* c, const Level& P, const float* R, const float* T,
     e.r.host = results_to(c, J, J_dev).host;
     e.r.jdev = J_dev;
     if (grad_T) {
-        e.a.sens = c->part + part_floats(P, V.variant);
+        e.a.sens = c->sens;
         e.a.gT_atomic = grad_T;
         launch_fill(grad_T, P.N(), 0.0f, c->stream);
         launch_image_march_sens(e.a, P.dyadic, march_ty(V.variant), e.a.cx, c->stream);
@@ -1060,7 +1077,8 @@ void ngf_destroy(ngf_ctx* c) {
         if (e) (void)hipEventDestroy(e);
     free_pyramid(c);
     log_free(c);
-    for (void* p : {static_cast<void*>(c->part), static_cast<void*>(c->dpart),
+    for (void* p : {static_cast<void*>(c->part), static_cast<void*>(c->sens),
+                    static_cast<void*>(c->dpart),
                     static_cast<void*>(c->spart), static_cast<void*>(c->gpart),
                     static_cast<void*>(c->jds),
                     static_cast<void*>(c->ly), static_cast<void*>(c->lg),
@@ -1534,11 +1552,8 @@ ngf_status ngf_eval_pair(ngf_ctx* c, const ngf_grid* g, const int32_t my[3], con
     }
     P.variant = kScatterVariant;  // the scatter form lives in a 3D-tile kernel
     P.dyadic = r;
-    // with room for e per voxel if there is any
-    if (ensure_scratch(c, P, march_fits(P) ? diff_floats(P) : 0) != NGF_OK)
-        if (const ngf_status st = ensure_scratch(c, P); st != NGF_OK) return st;
-    if ((grad_y || grad_T) && march_fits(P) &&
-        (!grad_T || c->part_cap >= diff_floats(P)))
+    if (const ngf_status st = ensure_scratch(c, P); st != NGF_OK) return st;
+    if ((grad_y || grad_T) && march_fits(P) && (!grad_T || sens_room(c, P)))
         return eval_diff(c, P, R, T, y, gscale, J, J_dev, grad_y, grad_T);
     return eval_scatter(c, P, R, T, y, gscale, J, J_dev, grad_y, grad_T, nullptr);
 }

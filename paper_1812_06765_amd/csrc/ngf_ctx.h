@@ -72,6 +72,9 @@ struct ngf_ctx {
     // evaluation scratch (sized for level 0 by ngf_build_pyramid / ngf_reserve)
     float* part = nullptr;
     size_t part_cap = 0;  // floats
+    // e per voxel of an explicit pair whose template gradient was asked for
+    float* sens = nullptr;
+    size_t sens_cap = 0;  // floats
     double* dpart = nullptr;
     size_t dpart_cap = 0;
     double* spart = nullptr;
