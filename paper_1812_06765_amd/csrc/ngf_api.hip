@@ -63,6 +63,26 @@ void dfree(void* p) {
     if (p) (void)hipFree(p);
 }
 
+// A buffer of `have` entries made `need` long (its contents are not kept), after
+// the work queued on it is done.  A failure leaves it as it was: the levels that
+// are built go on using it.  Only where both do not fit side by side is the old
+// one given up first; should it then not come back either, *p is null.
+template <class T>
+ngf_status regrow(ngf_ctx* c, T** p, size_t have, size_t need) {
+    T* q = nullptr;
+    if (dalloc(c, &q, need) == NGF_OK) {
+        dfree(*p);
+        *p = q;
+        return NGF_OK;
+    }
+    if (!*p || (c->faults & NGF_FAULT_ALLOC)) return NGF_E_OOM;
+    dfree(*p);
+    if (dalloc(c, p, need) == NGF_OK) return NGF_OK;
+    const std::string why = c->err;
+    (void)dalloc(c, p, have);
+    return fail(c, NGF_E_OOM, why);
+}
+
 bool params_ok(const ngf_params* p, std::string* why) {
     if (!(std::isfinite(p->alpha) && p->alpha >= 0.0)) return *why = "alpha must be >= 0", false;
     if (!(std::isfinite(p->tau) && p->tau > 0.0)) return *why = "tau must be > 0", false;
@@ -207,6 +227,12 @@ bool march_fits(const Level& P) {
     return ok;
 }
 
+// The pyramid is no longer there (its storage is kept for the next one).
+void drop_levels(ngf_ctx* c) {
+    c->lv.clear();
+    c->lb_level = -1;
+}
+
 ngf_status ensure_scratch(ngf_ctx* c, const Level& L) {
     size_t pf = 0, nt = 0;
     for (int v = 0; v < kNumVariants; ++v) {
@@ -223,30 +249,22 @@ ngf_status ensure_scratch(ngf_ctx* c, const Level& L) {
     const size_t nb = static_cast<size_t>(std::max({node_blocks_of(L, 0), node_blocks_of(L, 1), node_blocks_of(L, 2)}));
     if (pf > c->part_cap || nt > c->dpart_cap || nb > c->nblk_cap)
         HIPCHK(c, hipStreamSynchronize(c->stream));  // queued work may use the old buffers
-    if (pf > c->part_cap) {
-        dfree(c->part);
-        c->part = nullptr;
-        c->part_cap = 0;
-        if (dalloc(c, &c->part, pf) != NGF_OK) return NGF_E_OOM;
+    ngf_status st = NGF_OK;
+    if (pf > c->part_cap && (st = regrow(c, &c->part, c->part_cap, pf)) == NGF_OK)
         c->part_cap = pf;
-    }
-    if (nt > c->dpart_cap) {
-        dfree(c->dpart);
-        c->dpart = nullptr;
-        c->dpart_cap = 0;
-        if (dalloc(c, &c->dpart, nt) != NGF_OK) return NGF_E_OOM;
+    if (st == NGF_OK && nt > c->dpart_cap &&
+        (st = regrow(c, &c->dpart, c->dpart_cap, nt)) == NGF_OK)
         c->dpart_cap = nt;
-    }
-    if (nb > c->nblk_cap) {
-        dfree(c->spart);
-        dfree(c->gpart);
-        c->spart = c->gpart = nullptr;
-        c->nblk_cap = 0;
-        if (dalloc(c, &c->spart, nb) != NGF_OK) return NGF_E_OOM;
-        if (dalloc(c, &c->gpart, 2 * nb) != NGF_OK) return NGF_E_OOM;
+    if (st == NGF_OK && nb > c->nblk_cap &&
+        (st = regrow(c, &c->spart, c->nblk_cap, nb)) == NGF_OK &&
+        (st = regrow(c, &c->gpart, 2 * c->nblk_cap, 2 * nb)) == NGF_OK)
         c->nblk_cap = nb;
-    }
-    return NGF_OK;
+    if (!c->part) c->part_cap = 0;
+    if (!c->dpart) c->dpart_cap = 0;
+    if (!c->spart || !c->gpart) c->nblk_cap = 0;
+    // no evaluation without its scratch
+    if (st != NGF_OK && (!c->part_cap || !c->dpart_cap || !c->nblk_cap)) drop_levels(c);
+    return st;
 }
 
 ngf_status ensure_level_scratch(ngf_ctx* c, const Level& L) {
@@ -689,40 +707,11 @@ ngf_status autotune(ngf_ctx* c) {
     return st;
 }
 
-ngf_status pyramid_enqueue(ngf_ctx* c, const float* R, const float* T, const ngf_grid* g,
-                           int32_t host_ptrs) {
-    if (!R || !T || !g) return fail(c, NGF_E_ARG, "null R, T or grid");
-    const int L = c->p.levels, r = c->p.ratio;
-    int64_t N = 1;
-    int n0[3];  // level-0 deformation-grid nodes per axis
-    for (int d = 0; d < 3; ++d) {
-        if (!(std::isfinite(g->h[d]) && g->h[d] > 0.0))
-            return fail(c, NGF_E_ARG, "spacing must be positive");
-        if (g->m[d] <= 0 || g->m[d] > 32768 || g->m[d] % (1 << (L - 1)) != 0)
-            return fail(c, NGF_E_SHAPE,
-                        "each m_d must be at most 32768 and divisible by 2^(levels-1)");
-        if (c->node_grid[d] == 0 && g->m[d] % (r << (L - 1)) != 0)
-            return fail(c, NGF_E_SHAPE, "each m_d must be divisible by ratio * 2^(levels-1)");
-        n0[d] = c->node_grid[d] ? c->node_grid[d] : g->m[d] / r + 1;
-        if ((n0[d] - 1) % (1 << (L - 1)) != 0)
-            return fail(c, NGF_E_SHAPE,
-                        "node cells m^y_d - 1 must be divisible by 2^(levels-1)");
-        const int mc = g->m[d] >> (L - 1), nc = ((n0[d] - 1) >> (L - 1)) + 1;
-        if (mc < 4 || nc < 3)
-            return fail(c, NGF_E_SHAPE, "coarsest level needs >= 4 cells and >= 2 node cells");
-        if (2 * (n0[d] - 1) > g->m[d])
-            return fail(c, NGF_E_SHAPE,
-                        "at least 2 image cells per deformation cell: 2 (m^y_d - 1) <= m_d");
-        // the image tiles (32 points in y and z) must each meet every index
-        // set of Eq. 3 in at most two tiles per axis
-        if (g->m[d] > 16 * (n0[d] - 1))
-            return fail(c, NGF_E_SHAPE,
-                        "at most 16 image cells per deformation cell: m_d <= 16 (m^y_d - 1)");
-        N *= g->m[d];
-    }
-    if (N >= (static_cast<int64_t>(1) << 30))
-        return fail(c, NGF_E_SHAPE, "image too large (at most 2^30 - 1 voxels)");
-    c->lb_level = -1;
+// The levels of a grid that pyramid_enqueue has checked, with n0 nodes on the
+// finest: their storage, the scratch, and the work that fills them.
+ngf_status pyramid_queue(ngf_ctx* c, const float* R, const float* T, const ngf_grid* g,
+                         const int n0[3], int32_t host_ptrs) {
+    const int L = c->p.levels;
     c->lv.assign(L, Level{});
     for (int l = 0; l < L; ++l) {
         Level& lv = c->lv[l];
@@ -738,11 +727,7 @@ ngf_status pyramid_enqueue(ngf_ctx* c, const float* R, const float* T, const ngf
             for (int d = 0; d < 3; ++d) all = all && lv.m[d] % q == 0 && lv.my[d] == lv.m[d] / q + 1;
             if (all) lv.dyadic = q;
         }
-        const ngf_status e = bind_level_storage(c, l);
-        if (e != NGF_OK) {
-            c->lv.clear();
-            return e;
-        }
+        if (const ngf_status e = bind_level_storage(c, l); e != NGF_OK) return e;
     }
     if (const ngf_status st = ensure_scratch(c, c->lv[0]); st != NGF_OK) return st;
     if (ensure_lbfgs(c, static_cast<size_t>(3 * c->lv[0].Ny())) != NGF_OK) return NGF_E_OOM;
@@ -786,9 +771,48 @@ ngf_status pyramid_enqueue(ngf_ctx* c, const float* R, const float* T, const ngf
     return NGF_OK;
 }
 
+ngf_status pyramid_enqueue(ngf_ctx* c, const float* R, const float* T, const ngf_grid* g,
+                           int32_t host_ptrs) {
+    if (!R || !T || !g) return fail(c, NGF_E_ARG, "null R, T or grid");
+    const int L = c->p.levels, r = c->p.ratio;
+    int64_t N = 1;
+    int n0[3];  // level-0 deformation-grid nodes per axis
+    for (int d = 0; d < 3; ++d) {
+        if (!(std::isfinite(g->h[d]) && g->h[d] > 0.0))
+            return fail(c, NGF_E_ARG, "spacing must be positive");
+        if (g->m[d] <= 0 || g->m[d] > 32768 || g->m[d] % (1 << (L - 1)) != 0)
+            return fail(c, NGF_E_SHAPE,
+                        "each m_d must be at most 32768 and divisible by 2^(levels-1)");
+        if (c->node_grid[d] == 0 && g->m[d] % (r << (L - 1)) != 0)
+            return fail(c, NGF_E_SHAPE, "each m_d must be divisible by ratio * 2^(levels-1)");
+        n0[d] = c->node_grid[d] ? c->node_grid[d] : g->m[d] / r + 1;
+        if ((n0[d] - 1) % (1 << (L - 1)) != 0)
+            return fail(c, NGF_E_SHAPE,
+                        "node cells m^y_d - 1 must be divisible by 2^(levels-1)");
+        const int mc = g->m[d] >> (L - 1), nc = ((n0[d] - 1) >> (L - 1)) + 1;
+        if (mc < 4 || nc < 3)
+            return fail(c, NGF_E_SHAPE, "coarsest level needs >= 4 cells and >= 2 node cells");
+        if (2 * (n0[d] - 1) > g->m[d])
+            return fail(c, NGF_E_SHAPE,
+                        "at least 2 image cells per deformation cell: 2 (m^y_d - 1) <= m_d");
+        // the image tiles (32 points in y and z) must each meet every index
+        // set of Eq. 3 in at most two tiles per axis
+        if (g->m[d] > 16 * (n0[d] - 1))
+            return fail(c, NGF_E_SHAPE,
+                        "at most 16 image cells per deformation cell: m_d <= 16 (m^y_d - 1)");
+        N *= g->m[d];
+    }
+    if (N >= (static_cast<int64_t>(1) << 30))
+        return fail(c, NGF_E_SHAPE, "image too large (at most 2^30 - 1 voxels)");
+    c->lb_level = -1;
+    const ngf_status e = pyramid_queue(c, R, T, g, n0, host_ptrs);
+    if (e != NGF_OK) drop_levels(c);  // not all of them could be had or filled
+    return e;
+}
+
 ngf_status pyramid_finish(ngf_ctx* c) {
     if (*c->host_bad) {
-        c->lv.clear();
+        drop_levels(c);
         return fail(c, NGF_E_NONFINITE, "R or T holds NaN or infinity");
     }
     return autotune(c);

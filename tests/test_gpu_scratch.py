@@ -76,3 +76,30 @@ def test_no_room_for_the_sensitivities(gpu_lib):
             assert float((g - w).double().norm()) <= 1e-5 * float(w.double().norm())
         after = ctx.eval_J_grad(0, y)
         assert after[0] == before[0] and torch.equal(after[1], before[1])
+
+
+def test_failed_build_leaves_no_levels(gpu_lib):
+    """A build whose images fit the storage that is there but whose partial sums
+    do not: the levels it could not fill are not evaluated, and the next build
+    works (bits of a fresh context)."""
+    import torch
+    ngf = gpu_lib
+    m = (62, 62, 66)  # fewer voxels than 64^3 and more tiles
+    with ngf.Context(**KW) as ctx, ngf.Context(**KW) as other:
+        for c in (ctx, other):
+            c.set_kernel("by_size")
+        ctx.build_pyramid(*_images((64, 64, 64), 5))
+        R, T = _images(m, 6)
+        ctx.set_faults(ngf.Context.FAULT_ALLOC)
+        with pytest.raises(ngf.NgfError) as e:
+            ctx.build_pyramid(R, T)
+        assert e.value.status == ngf.E_OOM
+        ctx.set_faults(0)
+        with pytest.raises(ngf.NgfError) as e:
+            ctx.level_info(0)
+        assert e.value.status == ngf.E_STATE
+        ctx.build_pyramid(R, T)
+        other.build_pyramid(R, T)
+        y = other.identity(0) + 0.3
+        a, b = ctx.eval_J_grad(0, y), other.eval_J_grad(0, y)
+        assert a[0] == b[0] and torch.equal(a[1], b[1])
