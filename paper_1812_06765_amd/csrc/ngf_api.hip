@@ -1554,8 +1554,9 @@ ngf_status ngf_eval_pair(ngf_ctx* c, const ngf_grid* g, const int32_t my[3], con
     if (N >= (static_cast<int64_t>(1) << 31)) return fail(c, NGF_E_SHAPE, "image too large");
     Level& P = c->pair;
     bool same = true;
-    for (int d = 0; d < 3; ++d) same = same && P.m[d] == g->m[d] && P.h[d] == g->h[d];
-    if (!same || P.j0[0] == nullptr) {
+    for (int d = 0; d < 3; ++d)
+        same = same && P.m[d] == g->m[d] && P.h[d] == g->h[d] && P.my[d] == my[d];
+    if (!same || c->pair_owned.size() != 9) {  // fewer: an allocation failed
         HIPCHK(c, hipStreamSynchronize(c->stream));
         for (void* p : c->pair_owned) dfree(p);
         c->pair_owned.clear();
@@ -1564,12 +1565,13 @@ ngf_status ngf_eval_pair(ngf_ctx* c, const ngf_grid* g, const int32_t my[3], con
             P.h[d] = g->h[d];
             P.my[d] = my[d];
             P.hy[d] = P.m[d] * P.h[d] / (P.my[d] - 1);
-            if (dalloc(c, &P.j0[d], P.m[d]) != NGF_OK || dalloc(c, &P.w0[d], P.m[d]) != NGF_OK ||
-                dalloc(c, &P.w1[d], P.m[d]) != NGF_OK)
+            auto map = [&](auto** p) {
+                const ngf_status st = dalloc(c, p, P.m[d]);
+                if (st == NGF_OK) c->pair_owned.push_back(*p);
+                return st;
+            };
+            if (map(&P.j0[d]) != NGF_OK || map(&P.w0[d]) != NGF_OK || map(&P.w1[d]) != NGF_OK)
                 return NGF_E_OOM;
-            c->pair_owned.push_back(P.j0[d]);
-            c->pair_owned.push_back(P.w0[d]);
-            c->pair_owned.push_back(P.w1[d]);
             launch_index_map(P.j0[d], P.w0[d], P.w1[d], P.m[d], P.my[d], c->stream);
         }
         HIPCHK(c, hipGetLastError());

@@ -103,3 +103,23 @@ def test_failed_build_leaves_no_levels(gpu_lib):
         y = other.identity(0) + 0.3
         a, b = ctx.eval_J_grad(0, y), other.eval_J_grad(0, y)
         assert a[0] == b[0] and torch.equal(a[1], b[1])
+
+
+def test_pair_form_after_a_change_of_ratio(gpu_lib):
+    """The same images on another deformation grid, which a context without a
+    pyramid may be set to: the index maps are the new grid's (J as of a context of
+    that ratio, the gradients up to the rounding of atomic sums)."""
+    ngf = gpu_lib
+    m = (32, 40, 48)
+    R, T = _images(m, 7)
+    with ngf.Context(**KW) as ctx:
+        for ratio in (2, 4, 2):
+            ctx.set_params(ratio=ratio)
+            with ngf.Context(ratio=ratio, **KW) as other:
+                other.build_pyramid(R, T)
+                y = other.identity(0) + 0.3
+                want = other.eval_pair(R, T, y)
+            got = ctx.eval_pair(R, T, y)
+            assert got[0] == want[0]
+            for g, w in zip(got[1:], want[1:]):
+                assert float((g - w).double().norm()) <= 1e-6 * float(w.double().norm())
