@@ -154,8 +154,9 @@ ngf_status ngf_set_params(ngf_ctx* ctx, const ngf_params* p);
  * float64 in a fixed order and rounded once to float32, bit-identical for
  * identical inputs.  Also builds the per-axis index maps of every level
  * (Sec. 2.2, "Grid conversion": the index sets and weights are determined
- * beforehand per dimension) and sizes all scratch buffers.  The two images
- * are processed on two internal streams that join the context's stream.
+ * beforehand per dimension) and sizes all scratch buffers.  Images that are
+ * not in the device's own memory are copied on two internal streams that join
+ * the context's stream.
  *   R, T       input images on `g` ([m_x][m_y][m_z] float32)
  *   host_ptrs  0: R and T are device pointers; 1: host pointers (copied
  *              host-to-device on the two streams)

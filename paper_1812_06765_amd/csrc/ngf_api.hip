@@ -83,6 +83,17 @@ ngf_status regrow(ngf_ctx* c, T** p, size_t have, size_t need) {
     return fail(c, NGF_E_OOM, why);
 }
 
+// Whether p is memory of the current device, which its kernels may access in
+// place.  Memory of another kind (the host's, another device's) is left to copies,
+// which take any.
+bool on_device(const void* p) {
+    hipPointerAttribute_t a{};
+    int dev = 0;
+    const bool known = hipPointerGetAttributes(&a, p) == hipSuccess && hipGetDevice(&dev) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    return known && a.type == hipMemoryTypeDevice && a.device == dev;
+}
+
 bool params_ok(const ngf_params* p, std::string* why) {
     if (!(std::isfinite(p->alpha) && p->alpha >= 0.0)) return *why = "alpha must be >= 0", false;
     if (!(std::isfinite(p->tau) && p->tau > 0.0)) return *why = "tau must be > 0", false;
@@ -475,10 +486,12 @@ EvalArgs eval_args(ngf_ctx* c, const Level& L, const float* R, const float* T, c
     return e;
 }
 
-// Where the final reduction also puts its results (see ReduceArgs).
+// Where the final reduction also puts its results (see ReduceArgs); copy: J goes
+// there by a copy behind it (see on_device).
 struct Results {
     double* host = nullptr;
     double* jdev = nullptr;
+    double* copy = nullptr;
 };
 
 // Enqueue one evaluation on the context stream; results land in c->jds and
@@ -733,17 +746,18 @@ ngf_status pyramid_queue(ngf_ctx* c, const float* R, const float* T, const ngf_g
     if (ensure_lbfgs(c, static_cast<size_t>(3 * c->lv[0].Ny())) != NGF_OK) return NGF_E_OOM;
 
     // Level 0 copied and checked, then the successive 2x2x2 means, both images a
-    // launch.  Images in host memory come on two side streams.
+    // launch.  Images that are not in this device's memory come on two side streams.
     Level& F = c->lv[0];
     ImagePair p{{R, T}, {F.R, F.T}};
-    if (host_ptrs) {
-        HIPCHK(c, hipEventRecord(c->join[0], c->stream));
-        for (int k = 0; k < 2; ++k) {
-            HIPCHK(c, hipStreamWaitEvent(c->side[k], c->join[0], 0));
-            HIPCHK(c, hipMemcpyAsync(p.dst[k], p.src[k], static_cast<size_t>(F.N()) * sizeof(float),
-                                     hipMemcpyHostToDevice, c->side[k]));
-            HIPCHK(c, hipEventRecord(c->join[1 + k], c->side[k]));
-        }
+    const bool far[2] = {host_ptrs || !on_device(R), host_ptrs || !on_device(T)};
+    if (far[0] || far[1]) HIPCHK(c, hipEventRecord(c->join[0], c->stream));
+    for (int k = 0; k < 2; ++k) {
+        if (!far[k]) continue;
+        HIPCHK(c, hipStreamWaitEvent(c->side[k], c->join[0], 0));
+        HIPCHK(c, hipMemcpyAsync(p.dst[k], p.src[k], static_cast<size_t>(F.N()) * sizeof(float),
+                                 host_ptrs ? hipMemcpyHostToDevice : hipMemcpyDefault,
+                                 c->side[k]));
+        HIPCHK(c, hipEventRecord(c->join[1 + k], c->side[k]));
     }
     PyramidMaps maps{};
     for (int l = 0; l < L; ++l)
@@ -756,11 +770,11 @@ ngf_status pyramid_queue(ngf_ctx* c, const float* R, const float* T, const ngf_g
             maps.my[l][d] = lv.my[d];
         }
     launch_index_maps(maps, L, c->stream);
-    if (host_ptrs)
-        for (int k = 0; k < 2; ++k) {
-            HIPCHK(c, hipStreamWaitEvent(c->stream, c->join[1 + k], 0));
-            p.src[k] = p.dst[k];
-        }
+    for (int k = 0; k < 2; ++k) {
+        if (!far[k]) continue;
+        HIPCHK(c, hipStreamWaitEvent(c->stream, c->join[1 + k], 0));
+        p.src[k] = p.dst[k];
+    }
     *c->host_bad = 0;  // the last build that could set it has been waited for
     launch_take_images(p, F.N(), c->host_bad, c->stream);
     for (int l = 1; l < L; ++l) {
@@ -910,12 +924,15 @@ ngf_status check_level(const ngf_ctx* c, int level) {
 // Where J of an evaluation goes: to J_dev (device) and to the host if it is
 // wanted there.
 Results results_to(ngf_ctx* c, const double* J, double* J_dev) {
-    return {J ? c->host_jds : nullptr, J_dev};
+    const bool direct = J_dev && on_device(J_dev);
+    return {J ? c->host_jds : nullptr, direct ? J_dev : nullptr, direct ? nullptr : J_dev};
 }
 
 // J of the evaluation just queued (with results_to), read on the host
 // (synchronises) when wanted.
-ngf_status finish_J(ngf_ctx* c, double* J) {
+ngf_status finish_J(ngf_ctx* c, const Results& to, double* J) {
+    if (to.copy)
+        HIPCHK(c, hipMemcpyAsync(to.copy, c->jds, sizeof(double), hipMemcpyDefault, c->stream));
     if (!J) return NGF_OK;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     *J = c->host_jds[0];
@@ -937,8 +954,9 @@ ngf_status eval_diff(ngf_ctx* c, const Level& P, const float* R, const float* T,
     EvalArgs e = eval_args(c, V, R, T, y, grad_y, nullptr, nullptr);
     e.a.want_grad = 1;
     e.a.gscale = e.b.gscale = gscale;
-    e.r.host = results_to(c, J, J_dev).host;
-    e.r.jdev = J_dev;
+    const Results to = results_to(c, J, J_dev);
+    e.r.host = to.host;
+    e.r.jdev = to.jdev;
     if (grad_T) {
         e.a.sens = c->sens;
         e.a.gT_atomic = grad_T;
@@ -957,7 +975,7 @@ ngf_status eval_diff(ngf_ctx* c, const Level& P, const float* R, const float* T,
     HIPCHK(c, hipGetLastError());
     launch_reduce(e.r, c->stream);
     HIPCHK(c, hipGetLastError());
-    return finish_J(c, J);
+    return finish_J(c, to, J);
 }
 
 // Differentiation form on level L (its grids and index maps) with images R, T:
@@ -972,6 +990,7 @@ ngf_status eval_scatter(ngf_ctx* c, const Level& P, const float* R, const float*
     double* spart = sb ? sb->spart : c->spart;
     double* gpart = sb ? sb->gpart : c->gpart;
     const bool want = grad_y != nullptr || grad_T != nullptr;
+    const Results to = results_to(c, J, J_dev);
     if (!want && !sb) {
         // J alone (the autograd function's forward): the plain evaluation with
         // the image-pass kernel of the size rule (the context's scratch holds
@@ -979,10 +998,9 @@ ngf_status eval_scatter(ngf_ctx* c, const Level& P, const float* R, const float*
         Level V = P;
         const int v = variant_by_size(V);
         V.variant = variant_ok(V, v) && march_fits(V) ? v : P.variant;
-        const ngf_status e = enqueue_eval(c, V, R, T, y, nullptr, nullptr, nullptr,
-                                          results_to(c, J, J_dev));
+        const ngf_status e = enqueue_eval(c, V, R, T, y, nullptr, nullptr, nullptr, to);
         if (e != NGF_OK) return e;
-        return finish_J(c, J);
+        return finish_J(c, to, J);
     }
     if (grad_y) launch_fill(grad_y, 3 * P.Ny(), 0.0f, c->stream);
     if (grad_T) launch_fill(grad_T, P.N(), 0.0f, c->stream);
@@ -1038,11 +1056,11 @@ ngf_status eval_scatter(ngf_ctx* c, const Level& P, const float* R, const float*
     rd.half_hbary = 0.5 * hbary;
     rd.alpha = c->p.alpha;
     rd.out = c->jds;
-    rd.host = results_to(c, J, J_dev).host;
-    rd.jdev = J_dev;
+    rd.host = to.host;
+    rd.jdev = to.jdev;
     launch_reduce(rd, c->stream);
     HIPCHK(c, hipGetLastError());
-    return finish_J(c, J);
+    return finish_J(c, to, J);
 }
 
 }  // namespace ngf_host
@@ -1252,7 +1270,7 @@ ngf_status ngf_eval_J_grad(ngf_ctx* c, int32_t level, const float* y, double* J,
     const Level& L = c->lv[level];
     const bool read = J || DS;
     ngf_status e = enqueue_eval(c, L, L.R, L.T, y, grad, nullptr, nullptr,
-                                {read ? c->host_jds : nullptr, nullptr});
+                                {read ? c->host_jds : nullptr});
     if (e != NGF_OK) return e;
     if (read) {
         HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1283,7 +1301,7 @@ ngf_status ngf_lbfgs_reset(ngf_ctx* c, int32_t level, const float* y0) {
         HIPCHK(c, hipMemcpyAsync(c->ly, y0, n * sizeof(float), hipMemcpyDeviceToDevice,
                                  c->stream));
     ngf_status e = enqueue_eval(c, L, L.R, L.T, c->ly, c->lg, nullptr, nullptr,
-                                {c->host_jds, nullptr});
+                                {c->host_jds});
     if (e != NGF_OK) return e;
     const double hmin = std::min(L.h[0], std::min(L.h[1], L.h[2]));
     launch_lb_init(c->st, c->p.lbfgs_mem, hmin, c->jds, c->p.max_iter, c->p.early_stop,

@@ -108,3 +108,40 @@ def test_general_pass_chosen_after_the_build(gpu_lib):
             Jg, gg, _ = ctx.eval_J_grad(1, y)
             assert abs(Jg - J) <= 1e-5 * abs(J)
             assert float((gg - g).norm()) <= 1e-4 * float(g.norm())
+
+
+@pytest.mark.parametrize("where", ["pageable", "pinned", "one of them"])
+def test_memory_that_kernels_cannot_read_in_place(gpu_lib, where):
+    """Image and J_dev pointers that are not this device's memory, without
+    host_ptrs: copied, as every pointer was before kernels read and wrote them."""
+    import ctypes
+
+    import torch
+    ngf = gpu_lib
+    m = (16, 24, 20)
+    print(f"[build] {where}", flush=True)
+    gen = torch.Generator().manual_seed(9)
+    R, T = (100.0 * torch.randn(m, generator=gen) for _ in range(2))
+    if where == "pinned":
+        R, T = R.pin_memory(), T.pin_memory()
+    elif where == "one of them":
+        T = T.cuda()
+    with ngf.Context(alpha=0.1, tau=10.0, rho=10.0, levels=1) as ctx:
+        ctx.set_kernel("by_size")
+        g = ngf._grid(m, (1.0, 1.0, 1.0))
+        ctx._chk(ctx.lib.ngf_build_pyramid(ctx.h, ngf._ptr(R), ngf._ptr(T), ctypes.byref(g), 0))
+        a, b = ctx.level_images(0)
+        assert torch.equal(a.cpu(), R.cpu()) and torch.equal(b.cpu(), T.cpu())
+        y = ctx.identity(0) + 0.3
+        want = ctx.eval_pair(a, b, y)[0]
+        J = torch.zeros(1, dtype=torch.float64)
+        J = J.pin_memory() if where == "pinned" else J
+        my = (ctypes.c_int32 * 3)(*(v // 2 + 1 for v in m))
+        gy = torch.empty_like(y)
+        for grad in (None, ngf._ptr(gy)):
+            J.zero_()
+            ctx._chk(ctx.lib.ngf_eval_pair(ctx.h, ctypes.byref(g), ctypes.byref(my), ngf._ptr(a),
+                                           ngf._ptr(b), ngf._ptr(y), None, None, ngf._ptr(J), grad,
+                                           None))
+            torch.cuda.synchronize()
+            assert abs(float(J) - want) <= 1e-10 * abs(want)
