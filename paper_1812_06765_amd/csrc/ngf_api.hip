@@ -494,11 +494,29 @@ struct Results {
     double* copy = nullptr;
 };
 
+// The reference side of the NGF term of a level, which only the general pass
+// reads: formed when that pass is chosen (256^3: 100 us of a registration).
+void form_rn(ngf_ctx* c, Level& L) {
+    launch_rn(L.R, L.rn, L.m[0], L.m[1], L.m[2], L.h[0], L.h[1], L.h[2], c->p.rho, c->stream);
+}
+void need_rn(ngf_ctx* c, Level& L) {
+    if (L.rn_ok) return;
+    form_rn(c, L);
+    // under capture the launch is part of the graph and has not run yet
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    L.rn_ok = cap == hipStreamCaptureStatusNone;
+}
+
 // Enqueue one evaluation on the context stream; results land in c->jds and
 // (if grad != nullptr) in grad.
 ngf_status enqueue_eval(ngf_ctx* c, const Level& L, const float* R, const float* T,
                         const float* y, float* grad, const int* gate = nullptr,
                         LbState* decide = nullptr, const Results& to = {}) {
+    // (not there yet where the general pass was chosen under capture)
+    if (is_gen(L.variant) && !L.rn_ok)
+        for (Level& l : c->lv)
+            if (&l == &L) need_rn(c, l);
     EvalArgs e = eval_args(c, L, R, T, y, grad, gate, decide);
     e.r.host = to.host;
     e.r.jdev = to.jdev;
@@ -628,20 +646,6 @@ bool sens_room(ngf_ctx* c, const Level& L) {
     }
     c->sens_cap = n;
     return true;
-}
-
-// The reference side of the NGF term of a level, which only the general pass
-// reads: formed when that pass is chosen (256^3: 100 us of a registration).
-void form_rn(ngf_ctx* c, Level& L) {
-    launch_rn(L.R, L.rn, L.m[0], L.m[1], L.m[2], L.h[0], L.h[1], L.h[2], c->p.rho, c->stream);
-}
-void need_rn(ngf_ctx* c, Level& L) {
-    if (L.rn_ok) return;
-    form_rn(c, L);
-    // under capture the launch is part of the graph and has not run yet
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
-    L.rn_ok = cap == hipStreamCaptureStatusNone;
 }
 
 // Pick the image-pass variant of every level: forced, cached for this shape,

@@ -145,3 +145,68 @@ def test_memory_that_kernels_cannot_read_in_place(gpu_lib, where):
                                            None))
             torch.cuda.synchronize()
             assert abs(float(J) - want) <= 1e-10 * abs(want)
+
+
+def test_general_pass_chosen_under_capture(gpu_lib):
+    """A choice of the general pass that is only recorded has formed nothing: an
+    evaluation before the first replay, and the replays, have the values of a
+    choice made outside."""
+    import torch
+    ngf = gpu_lib
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    R, T = (100.0 * torch.randn((32, 48, 40), device="cuda", generator=gen) for _ in range(2))
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s), ngf.Context(alpha=0.1, tau=10.0, rho=10.0, levels=1) as ctx:
+        ctx.set_kernel("by_size")
+        ctx.build_pyramid(R, T)
+        y = ctx.identity(0) + 0.3
+        g = torch.empty_like(y)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            ctx.set_kernel("general")
+            ctx.eval_J_grad_async(0, y, g)
+        eager = ctx.eval_J_grad(0, y)
+        with ngf.Context(alpha=0.1, tau=10.0, rho=10.0, levels=1) as other:
+            other.set_kernel("general")
+            other.build_pyramid(R, T)
+            want = other.eval_J_grad(0, y)
+        assert eager[0] == want[0] and torch.equal(eager[1], want[1])
+        for _ in range(3):
+            g.zero_()
+            graph.replay()
+            s.synchronize()
+            assert torch.equal(g, want[1])
+
+
+def test_pair_form_under_capture(gpu_lib):
+    """The pair form captured after a call for J alone, when there is no room yet
+    for the template gradient's sensitivities, and after one with them: replays
+    against the eager results (atomic sums: up to rounding)."""
+    import torch
+    ngf = gpu_lib
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    R, T = (100.0 * torch.randn((32, 48, 40), device="cuda", generator=gen) for _ in range(2))
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s), ngf.Context(alpha=0.1, tau=10.0, rho=10.0, levels=1) as ctx:
+        ctx.set_kernel("by_size")
+        ctx.build_pyramid(R, T)
+        y = ctx.identity(0) + 0.3
+        want = ctx.eval_J_grad(0, y)
+        J = torch.zeros(1, dtype=torch.float64, device="cuda")
+        ctx.eval_pair(R, T, y, grad_y=False, grad_T=False)
+        for warm in (False, True):
+            if warm:
+                ref = ctx.eval_pair(R, T, y)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=s):
+                _, gy, gT = ctx.eval_pair(R, T, y, J_dev=J, sync=False)
+            for _ in range(3):
+                J.zero_()
+                graph.replay()
+                s.synchronize()
+                assert abs(float(J) - want[0]) <= 1e-10 * abs(want[0])
+                assert float((gy - want[1]).norm()) <= 1e-5 * float(want[1].norm())
+                if warm:
+                    assert float((gT - ref[2]).norm()) <= 1e-5 * float(ref[2].norm())
