@@ -481,16 +481,15 @@ ngf_status ngf_set_faults(ngf_ctx* ctx, int32_t flags);
  *     level one L-BFGS round of every pair is one fixed sequence of batched
  *     launches (each covering all pairs through a block table), captured as
  *     a hipGraph and replayed on the batch's own stream until every pair's
- *     level has ended.  Image-pass variants by the size rule over the
- *     voxels of all pairs at the level, with chunks fitted to each pair's part
- *     of the device; ngf_batch_set_kernel overrides (the timed selection then
- *     takes one table shared by the pairs).
+ *     level has ended.  Image-pass variants by each pair's own level size
+ *     (below 64 Ki voxels 8, below 128 Ki 11, below 1280 Ki 4, below 8 Mi 10,
+ *     else 6); ngf_batch_set_kernel overrides (the timed selection then takes one
+ *     table shared by the pairs).
  *   1 threads: a host scheduler hands pairs, largest voxel count first, to
  *     `workers` threads (1..16), each with a context on its own stream;
  *     variants by the size rule unless set.
- * In both, with a variant set, every pair's result equals the single-pair
- * ngf_register result for the same image-pass variants bit for bit; with the
- * graph mode's default it equals it up to rounding.
+ * In both, every pair's result equals the single-pair ngf_register result
+ * for the same image-pass variants bit for bit, whatever the other pairs are.
  *   ngf_batch_create      params as for ngf_create; workers as above (used
  *                         by mode 1); the device is the current one
  *   ngf_batch_set_kernel  variant as for ngf_set_kernel, for every pair

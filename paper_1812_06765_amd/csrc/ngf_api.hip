@@ -148,10 +148,8 @@ Geo geometry(const Level& L, int variant) {
         g.tz = march_tz(variant);
         g.tx = march_cx(variant);
         if (g.tx == 0)
-            g.tx = L.chunk > 0
-                       ? std::min(L.chunk, tiles(L.m[0], 4) * 4)
-                       : fit_chunk(L.m[0], int64_t{tiles(L.m[1], g.ty)} * tiles(L.m[2], g.tz), 4,
-                                   4, image_march_slots(g.ty, g.tz));
+            g.tx = fit_chunk(L.m[0], int64_t{tiles(L.m[1], g.ty)} * tiles(L.m[2], g.tz), 4, 4,
+                             image_march_slots(g.ty, g.tz));
     }
     g.ntx = tiles(L.m[0], g.tx);
     g.nty = tiles(L.m[1], g.ty);
@@ -172,34 +170,6 @@ Geo geometry(const Level& L, int variant) {
     }
     return g;
 }
-// As fit_chunk, for one launch over many levels: the rounds of all their
-// workgroups times the planes of the longest chunk.  A level's chunks are of like
-// length.
-void batch_chunks(const std::vector<Level*>& levels, int variant) {
-    const int slots = image_march_slots(march_ty(variant), march_tz(variant));
-    int len = 4;
-    auto chunk = [](const Level& L, int target) {
-        const int k = tiles(L.m[0], target);
-        return tiles(tiles(L.m[0], k), 4) * 4;
-    };
-    for (const Level* L : levels) len = std::max(len, tiles(L->m[0], 4) * 4);
-    int best = 4;
-    int64_t best_cost = -1;
-    for (int target = 4; target <= len; target += 4) {
-        int64_t n = 0;
-        int longest = 0;
-        for (const Level* L : levels) {
-            const int cx = chunk(*L, target);
-            longest = std::max(longest, cx);
-            n += int64_t{tiles(L->m[0], cx)} * tiles(L->m[1], march_ty(variant)) *
-                 tiles(L->m[2], march_tz(variant));
-        }
-        const int64_t cost = (n + slots - 1) / slots * (longest + 4);
-        if (best_cost < 0 || cost < best_cost) best = target, best_cost = cost;
-    }
-    for (Level* L : levels) L->chunk = chunk(*L, best);
-}
-
 int64_t part_floats(const Level& L, int variant) {
     const Geo g = geometry(L, variant);
     return g.ntiles() * 3 * int64_t{g.px} * g.py * g.pz;
@@ -276,13 +246,6 @@ ngf_status ensure_scratch(ngf_ctx* c, const Level& L) {
     // no evaluation without its scratch
     if (st != NGF_OK && (!c->part_cap || !c->dpart_cap || !c->nblk_cap)) drop_levels(c);
     return st;
-}
-
-ngf_status ensure_level_scratch(ngf_ctx* c, const Level& L) {
-    const bool fits = static_cast<size_t>(part_floats(L, L.variant)) <= c->part_cap &&
-                      static_cast<size_t>(geometry(L, L.variant).ntiles()) <= c->dpart_cap &&
-                      static_cast<size_t>(node_blocks(L)) <= c->nblk_cap;
-    return fits ? NGF_OK : ensure_scratch(c, L);
 }
 
 ngf_status ensure_lbfgs(ngf_ctx* c, size_t n) {
@@ -612,12 +575,34 @@ void tune_cache_store(const std::string& key, int v) {
 // 53 / 52, 256^3 881 / 198 / 194: a small level has too few marching
 // workgroups to fill the device and is bound by their chain of planes, a
 // large one by the halo's work.
-int variant_for(const Level& L, int64_t voxels) {
+int variant_by_size(const Level& L) {
     if (!L.dyadic) return kMarchGen;
-    if (voxels >= (int64_t{1} << 20)) return kMarchSqFit;
-    return voxels >= 3 * (int64_t{1} << 17) ? kMarch32Fit : kTile3DTiny;
+    if (L.N() >= (int64_t{1} << 20)) return kMarchSqFit;
+    return L.N() >= 3 * (int64_t{1} << 17) ? kMarch32Fit : kTile3DTiny;
 }
-int variant_by_size(const Level& L) { return variant_for(L, L.N()); }
+
+// The same for a level that shares its launches with those of other pairs: by its
+// own size alone, so that a pair's result does not depend on which the others are.
+// Chunks fitted to one pair's workgroups are short ones, with many halo planes,
+// and the device is filled without them.  Batched evaluations of ratio 2 on gfx950
+// through the entry point, us (about 60 of the host's), variants 8 / 11 / 4 / 10 /
+// 6 / 13: 12 pairs of 32^3 149 / 152 / 157 / 178 / 216 / 153, of 48^3 201 / 167 /
+// 173 / 193 / 241 / 171, of 64^3 315 / 231 / 202 / 220 / 266 / 233, of 128^3 1607 /
+// 600 / 567 / 546 / 556 / 604, of 224^3 11774 / 2092 / 2365 / 2151 / 2058 / 2185;
+// a pair of 48^3 alone 74 / 85 / 95 / 116 / 155 / 87, of 128^3 184 / 108 / 108 /
+// 126 / 176 / 118.  4, 10, 11 and 6 are one kernel, so their pairs share a launch;
+// 8 begins where few pairs gain by it what many lose.  Registrations against a
+// variant and chunks chosen over all pairs of a level: 12 pairs of 96 to 160 points
+// an axis 10.58 -> 10.30 ms, of 80 to 128 7.5 -> 6.7; where the sizes lie on both
+// sides of 64 Ki, 12 of 40 to 64 2.95 -> 3.25, 4 of 48 to 72 2.04 -> 2.19.
+int batch_variant(const Level& L) {
+    if (!L.dyadic) return kMarchGen;
+    const int64_t Ki = L.N() >> 10;
+    if (Ki < 64) return kTile3DTiny;
+    if (Ki < 128) return kMarch32Fit;
+    if (Ki < 1280) return kMarch32x8;
+    return Ki < 8192 ? kMarch32x16 : kMarch32x32;
+}
 
 // Image-pass variant of the differentiation form where the template gradient
 // is wanted: the marching tiles store the sensitivities it needs.

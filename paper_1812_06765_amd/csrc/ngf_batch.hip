@@ -12,9 +12,9 @@
 // gathered control blocks between batches of replays and stops when every
 // pair's level has ended.  The kernels run the single-pair bodies with each
 // pair's own arguments, so a pair's result equals its single-pair
-// registration with the same image-pass variants, bit for bit.  Variants are
-// picked per level shape by the timed selection, with one table shared by
-// all pairs of the batch.
+// registration with the same image-pass variants, bit for bit, whatever the
+// other pairs are.  Variants by a rule on each level's own size, or as the
+// caller sets them (the timed selection then has one table for all pairs).
 //
 // Thread mode.  A host scheduler hands pairs, largest first, to worker
 // threads, each with its own context and stream; the device overlaps them.
@@ -52,7 +52,7 @@ struct ngf_batch {
     ngf_params p{};
     int device = 0;
     int mode = 0;          // 0 graph, 1 worker threads
-    int variant = -3;      // -3: the mode's default (size rule, graph: over the batch)
+    int variant = -3;      // -3: the mode's default (a size rule)
     std::vector<Worker> workers;
     hipStream_t stream = nullptr;
     hipEvent_t start = nullptr;
@@ -145,28 +145,9 @@ ngf_status build_pairs(ngf_batch* b, int np, const float* const* R, const float*
         if (s != NGF_OK) return bfail(b, s, "pair " + std::to_string(i) + ": " + c->err);
         b->tune = c->tune_cache;
     }
-    // Default selection: one launch covers all pairs of a level, so the size
-    // rule takes the voxels of all of them, and their chunks along x are chosen
-    // together: longer ones than a pair alone would take, with fewer halo planes.
-    // Twelve pairs of 96 to 160 points an axis: image passes of a registration
-    // 8.0 -> 5.5 ms against the selection timed pair by pair, which split a
-    // level over up to four variants' launches.
-    for (int lev = 0; b->variant == -3 && lev < b->p.levels; ++lev) {
-        int64_t total = 0;
-        for (int i = 0; i < np; ++i) total += b->pctx[i]->lv[lev].N();
-        std::vector<Level*> march;
-        for (int i = 0; i < np; ++i) {
-            Level& L = b->pctx[i]->lv[lev];
-            L.variant = variant_for(L, total);
-            if (is_march(L.variant)) march.push_back(&L);
-        }
-        if (!march.empty()) batch_chunks(march, march[0]->variant);
-        for (int i = 0; i < np; ++i) {
-            const Level& L = b->pctx[i]->lv[lev];
-            if (const ngf_status s = ensure_level_scratch(b->pctx[i], L); s != NGF_OK)
-                return bfail(b, s, "pair " + std::to_string(i) + ": " + b->pctx[i]->err);
-        }
-    }
+    if (b->variant == -3)
+        for (int i = 0; i < np; ++i)
+            for (Level& L : b->pctx[i]->lv) L.variant = batch_variant(L);
     b->nbuilt = np;
     return NGF_OK;
 }
@@ -190,7 +171,7 @@ ngf_status upload_tables(ngf_batch* b, const std::vector<char>& host, size_t byt
     return NGF_OK;
 }
 
-// One image pass per variant group, each covering its pairs' blocks.
+// One image pass per group, each covering its pairs' blocks.
 void launch_image_groups(const std::vector<LevelTables::Group>& groups, const char* d,
                          size_t o_args, int ratio, hipStream_t s) {
     for (const auto& g : groups) {
@@ -206,11 +187,18 @@ void launch_image_groups(const std::vector<LevelTables::Group>& groups, const ch
     }
 }
 
-// The variant group of a level in a block-table set.
+// Variants that are one kernel: marching ones with the same (y, z) tile differ in
+// the chunk along x only, which is an argument.
+bool same_kernel(int v, int w) {
+    return v == w || (is_march(v) && is_march(w) && march_ty(v) == march_ty(w) &&
+                      march_tz(v) == march_tz(w));
+}
+
+// The group of a level in a block-table set.
 LevelTables::Group& group_of(LevelTables& t, const Level& lv) {
     const bool p2 = pow2(lv.h[0]) && pow2(lv.h[1]) && pow2(lv.h[2]);
     for (auto& gg : t.groups)
-        if (gg.variant == lv.variant && gg.pow2 == p2) return gg;
+        if (same_kernel(gg.variant, lv.variant) && gg.pow2 == p2) return gg;
     t.groups.push_back(LevelTables::Group{lv.variant, p2, {}, 0});
     return t.groups.back();
 }

@@ -33,9 +33,6 @@ struct Level {
     // every axis has m^y = m/r + 1 for one r in {2, 4}: 2 or 4; otherwise 0
     // (then only the general image pass applies)
     int dyadic = 2;
-    // x chunk of the fitted marching variants: in a batch whose default selection
-    // holds, chosen with the other pairs (0: fitted to this level alone)
-    int chunk = 0;
     int64_t N() const { return static_cast<int64_t>(m[0]) * m[1] * m[2]; }
     int64_t Ny() const { return static_cast<int64_t>(my[0]) * my[1] * my[2]; }
 };
@@ -155,12 +152,8 @@ int64_t node_blocks(const Level& L);
 ngf_status pyramid_enqueue(ngf_ctx* c, const float* R, const float* T, const ngf_grid* g,
                            int32_t host_ptrs);
 ngf_status pyramid_finish(ngf_ctx* c);
-// Image-pass variant of a level from the voxels that a launch covers.
-int variant_for(const Level& L, int64_t voxels);
-// Chooses the x chunks of levels in one launch of a fitted marching variant.
-void batch_chunks(const std::vector<Level*>& levels, int variant);
-// Scratch for a level's chosen variant and chunk.
-ngf_status ensure_level_scratch(ngf_ctx* c, const Level& L);
+// Image-pass variant of a level in launches that many pairs share.
+int batch_variant(const Level& L);
 ngf_status fail(ngf_ctx* c, ngf_status s, const std::string& msg);
 
 // Arguments of the three kernels of one evaluation at level L of context c:
