@@ -116,7 +116,9 @@ __device__ inline Range omega_range(const Maps& a, int d, int j) {
 // a node plane is complete its sums go to LDS, where a thread per node adds its
 // index sets along y and z; the two buffers need one barrier a node plane.
 // U: points of an index set along y and z (4 or 8 for ratios 2 and 4, whose
-// weights then stay in registers), 0 where they differ from node to node.
+// weights then stay in registers; the cell that an end node does not have reads
+// zeros behind the window: one of the set's own values, with weight 0, would make
+// an infinity a NaN), 0 where they differ from node to node.
 // 256 x 256 x 192: 37 us at ratio 2 and 41 at ratio 4, against 333 and 629 with
 // a thread a node that read its whole index set; the read alone takes 29 us.
 constexpr int kPBlocks = 2048, kGatherBlocks = 512;
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_PT_gather(Maps a, GatherTile
                                                               const float* __restrict__ z,
                                                               float* __restrict__ out) {
     constexpr int K = kGatherPos;
-    __shared__ float win[2][3][kGatherWindow];
+    __shared__ float win[2][3][kGatherWindow + U / 2];
     const int plane = a.m[1] * a.m[2];
     const int64_t N = static_cast<int64_t>(a.m[0]) * plane;
     const int64_t nyz = static_cast<int64_t>(a.n[1]) * a.n[2], Ny = a.n[0] * nyz;
@@ -168,6 +170,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_PT_gather(Maps a, GatherTile
         }
     }
     const int base = (ry.lo - iy0) * wz + (rz.lo - iz0);
+    if constexpr (U > 0) {
+        constexpr int H = U / 2;
+        if (t < 6 * H) win[t / (3 * H)][t / H % 3][kGatherWindow + t % H] = 0.0f;
+    }
     int buf = 0;
     float A[3][K] = {}, Bn[3][K] = {}, v[3][K];
     auto load = [&](int ix) {
@@ -188,14 +194,18 @@ __global__ __launch_bounds__(kGatherThreads) void k_PT_gather(Maps a, GatherTile
             if constexpr (U > 0) {
 #pragma unroll
                 for (int p = 0; p < U; ++p) {
-                    // a row beyond the window has weight 0: read the last one
-                    const int row = base + min(p, ry.hi - ry.lo - 1) * wz;
+                    // the row's points in the node's first cell and in its second
+                    const int first = p < ry.hi - ry.lo ? base + p * wz : kGatherWindow;
+                    const int second = p < ry.hi - ry.lo && rz.hi - rz.lo == U ? first + U / 2
+                                                                               : kGatherWindow;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
+                        const float *a0 = win[buf][c] + first, *a1 = win[buf][c] + second;
                         float rs = 0.0f;
 #pragma unroll
-                        for (int q = 0; q < U; ++q)
-                            rs = fmaf(uz[q], win[buf][c][row + min(q, rz.hi - rz.lo - 1)], rs);
+                        for (int q = 0; q < U / 2; ++q) rs = fmaf(uz[q], a0[q], rs);
+#pragma unroll
+                        for (int q = 0; q < U / 2; ++q) rs = fmaf(uz[U / 2 + q], a1[q], rs);
                         r[c] = fmaf(uy[p], rs, r[c]);
                     }
                 }

@@ -45,3 +45,32 @@ def test_P_and_gather(gpu_lib, m, ratio, nodes):
         got = ctx.apply_PT(0, torch.from_numpy(z).cuda(), "gather").cpu().numpy()
         want = O.apply_PT(z.astype(np.float64), m, my)
         assert np.max(np.abs(got.astype(np.float64) - want)) <= 1e-5 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("m,ratio", [((8, 10, 12), 2), ((6, 70, 142), 2), ((8, 12, 16), 4),
+                                     ((8, 64, 72), 4)])
+def test_gather_of_an_infinity(gpu_lib, m, ratio):
+    """An infinity reaches the nodes whose index sets hold its point, as an
+    infinity, and no other value: at the grid's ends, next to them and inside."""
+    import torch
+    ngf = gpu_lib
+    print(f"[gridconv] infinity m={m} ratio={ratio}", flush=True)
+    rng = np.random.default_rng(30)
+    blank = torch.zeros(m, device="cuda")
+    with ngf.Context(alpha=1.0, tau=1.0, rho=1.0, levels=1, ratio=ratio) as ctx:
+        ctx.build_pyramid(blank, blank)
+        z = torch.from_numpy(rng.standard_normal((3,) + m).astype(np.float32)).cuda()
+        places = [(x, y, w) for x in (0, m[0] - 1) for y in (0, ratio - 1, m[1] - 1)
+                  for w in (0, ratio, m[2] - ratio, m[2] - 1)] + [tuple(v // 2 for v in m)]
+        for i in places:
+            for inf in (float("inf"), float("-inf")):
+                one, without = torch.zeros_like(z), z.clone()
+                one[(slice(None),) + i] = 1.0
+                without[(slice(None),) + i] = 0.0
+                bad = z.clone()
+                bad[(slice(None),) + i] = inf
+                reached = ctx.apply_PT(0, one, "redblack") != 0
+                assert int(reached.sum()) == 24
+                got, rest = ctx.apply_PT(0, bad), ctx.apply_PT(0, without)
+                assert bool((got[reached] == inf).all())
+                assert torch.equal(got[~reached], rest[~reached])
