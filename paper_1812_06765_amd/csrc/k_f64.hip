@@ -49,8 +49,8 @@ struct Grid64 {
     int m[3], my[3];
     double h[3], hy[3];
     double ih[3];    // 1 / h
-    double i2h[3];   // 1 / (2 h)
-    double ihy2[3];  // 1 / hy^2
+    double h2[3], i2h[3];     // 2 h and its reciprocal
+    double hy2[3], ihy2[3];  // hy^2 and its reciprocal
     int64_t n, ny;
     int pow2h;       // every 1 / h is exact
     int cx;          // image planes a workgroup
@@ -82,6 +82,11 @@ __device__ inline void index_map(int i, int m, int my, int& j0, double& w0, doub
     w0 = static_cast<double>(den - r) / static_cast<double>(den);
 }
 
+// Quotient by 2 h along an axis.
+__device__ inline double over_2h(const Grid64& g, double v, int d) {
+    return quotient(v, g.h2[d], g.i2h[d]);
+}
+
 // Displacement u = y - X at node (j) of component c, X_d = j_d h^y_d.
 __device__ inline double disp(const double* yc, const Grid64& g, const int j[3], int c) {
     const int64_t k = (static_cast<int64_t>(j[0]) * g.my[1] + j[1]) * g.my[2] + j[2];
@@ -99,7 +104,7 @@ __device__ inline double laplacian(const Grid64& g, const int j[3], F value) {
         int jp[3] = {j[0], j[1], j[2]}, jm[3] = {j[0], j[1], j[2]};
         jp[d] = min(j[d] + 1, g.my[d] - 1);
         jm[d] = max(j[d] - 1, 0);
-        out += (value(jp) - 2.0 * u0 + value(jm)) * g.ihy2[d];
+        out += quotient_with_infinities(value(jp) - 2.0 * u0 + value(jm), g.hy2[d], g.ihy2[d]);
     }
     return out;
 }
@@ -262,11 +267,11 @@ __global__ __launch_bounds__(kT) void k64_ngf(Grid64 g, const double* __restrict
         const int64_t np = at(x + 1);
         const double T2 = Ty[np];
         const float R2 = R[np];
-        const double gT[3] = {(T2 - T0) * g.i2h[0], (Ty[n + yp] - Ty[n + ym]) * g.i2h[1],
-                              (Ty[n + zp] - Ty[n + zm]) * g.i2h[2]};
+        const double gT[3] = {over_2h(g, T2 - T0, 0), over_2h(g, Ty[n + yp] - Ty[n + ym], 1),
+                              over_2h(g, Ty[n + zp] - Ty[n + zm], 2)};
         auto dR = [](float p, float m) { return static_cast<double>(p) - static_cast<double>(m); };
-        const double gR[3] = {dR(R2, R0) * g.i2h[0], dR(R[n + yp], R[n + ym]) * g.i2h[1],
-                              dR(R[n + zp], R[n + zm]) * g.i2h[2]};
+        const double gR[3] = {over_2h(g, dR(R2, R0), 0), over_2h(g, dR(R[n + yp], R[n + ym]), 1),
+                              over_2h(g, dR(R[n + zp], R[n + zm]), 2)};
         const double nT = sqrt(gT[0] * gT[0] + gT[1] * gT[1] + gT[2] * gT[2] + tau * tau);
         const double nR = sqrt(gR[0] * gR[0] + gR[1] * gR[1] + gR[2] * gR[2] + rho * rho);
         const double c = gT[0] * gR[0] + gT[1] * gR[1] + gT[2] * gR[2] + tau * rho;
@@ -402,7 +407,7 @@ __global__ __launch_bounds__(kGThreads, 4) void k64_gather(
             const double ey = (ylo ? -w[1] : w[1]) - (yup ? -w[2] : w[2]);
             const double ez = (zlo ? -w[3] : w[3]) - (zup ? -w[4] : w[4]);
             const double vx2 = ix == g.m[0] - 1 ? -w[0] : w[0];
-            const double e = (vx0 - vx2) * g.i2h[0] + ey * g.i2h[1] + ez * g.i2h[2];
+            const double e = over_2h(g, vx0 - vx2, 0) + over_2h(g, ey, 1) + over_2h(g, ez, 2);
             vx0 = vx1;
             vx1 = w[0];
             double z[3];
@@ -500,8 +505,10 @@ extern "C" ngf_status ngf_eval_J_grad_f64(ngf_ctx* c, int32_t level, const doubl
         g.h[d] = L.h[d];
         g.hy[d] = L.hy[d];
         g.ih[d] = 1.0 / L.h[d];
-        g.i2h[d] = 1.0 / (2.0 * L.h[d]);
-        g.ihy2[d] = 1.0 / (L.hy[d] * L.hy[d]);
+        g.h2[d] = 2.0 * L.h[d];
+        g.i2h[d] = 1.0 / g.h2[d];
+        g.hy2[d] = L.hy[d] * L.hy[d];
+        g.ihy2[d] = 1.0 / g.hy2[d];
     }
     g.n = L.N();
     g.ny = L.Ny();

@@ -213,13 +213,16 @@ __device__ inline void lb_solve_wave(LbState* st, double* jds, SolveLds& w) {
         }
         const double rg = l == kBasisG ? gn2 : row(kBasisG);
         const int own = l < count ? w.order[l] : w.order[0];
-        const double inv = 1.0 / G[own * kBasis + kSlots + own];
+        const double st_own = G[own * kBasis + kSlots + own], inv = 1.0 / st_own;
+        auto over_st = [&](double v, int k) {
+            return quotient_with_infinities(v, lb_lane(st_own, k), lb_lane(inv, k));
+        };
         q = l == kBasisG ? 1.0 : 0.0;
         double al = 0.0;
 #pragma unroll
         for (int k = kSlots - 1; k >= 0; --k) {
             if (k >= count) continue;
-            const double a = lb_basis_sum(q * rs[k]) * lb_lane(inv, k);
+            const double a = over_st(lb_basis_sum(q * rs[k]), k);
             if (l == k) al = a;
             if (l == kSlots + slot[k]) q -= a;
         }
@@ -228,7 +231,7 @@ __device__ inline void lb_solve_wave(LbState* st, double* jds, SolveLds& w) {
 #pragma unroll
         for (int k = 0; k < kSlots; ++k) {
             if (k >= count) continue;
-            const double b = lb_basis_sum(q * rt[k]) * lb_lane(inv, k);
+            const double b = over_st(lb_basis_sum(q * rt[k]), k);
             const double a = lb_lane(al, k);
             if (l == slot[k]) q += a - b;
         }

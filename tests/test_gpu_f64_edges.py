@@ -41,3 +41,37 @@ def test_f64_edges(gpu_lib, m, ratio, nodes, h):
         Jv, none, _ = ctx.eval_J_grad_f64(0, yt, want_grad=False)
         assert abs(J - Jo) <= 1e-10 * abs(Jo) and Jv == J and none is None
         assert np.linalg.norm(g.cpu().numpy() - go) <= 1e-10 * np.linalg.norm(go)
+
+
+def test_f64_quotients_are_correctly_rounded(gpu_lib):
+    """Blank images and single displaced nodes: grad J two nodes from one along an
+    axis is alpha hbar^y ((u / h^y^2) / h^y^2), one quotient of another, in which
+    a product with a rounded reciprocal shows.  Spacings whose squares are no
+    powers of two, node positions and displacements exact."""
+    import torch
+    ngf = gpu_lib
+    rng = np.random.default_rng(8)
+    m, h, alpha = (48, 48, 48), (0.75, 1.25, 2.5), 1.0
+    blank = torch.zeros(m, device="cuda")
+    with ngf.Context(alpha=alpha, tau=10.0, rho=10.0, levels=1) as ctx:
+        ctx.build_pyramid(blank, blank, h)
+        my, hy = ctx.level_info(0).my, ctx.level_info(0).hy
+        assert hy == (1.5, 2.5, 5.0)
+        y = np.stack(np.meshgrid(*[np.arange(my[d]) * hy[d] for d in range(3)], indexing="ij"))
+        at = [(a, b, c) for a in (4, 12, 20) for b in (4, 12, 20) for c in (4, 12, 20)]
+        u = 1.0 + rng.integers(0, 2 ** 40, size=(len(at), 3)) * 2.0 ** -41
+        for k, p in enumerate(at):
+            y[(slice(None),) + p] += u[k]
+        _, g, _ = ctx.eval_J_grad_f64(0, torch.from_numpy(y).cuda())
+        g = g.cpu().numpy()
+    scale = alpha * (hy[0] * hy[1] * hy[2])
+    wrong = 0
+    for k, p in enumerate(at):
+        for c in range(3):
+            for d in range(3):
+                want = scale * ((u[k, c] / (hy[d] * hy[d])) / (hy[d] * hy[d]))
+                for s in (-2, 2):
+                    q = list(p)
+                    q[d] += s
+                    wrong += g[(c,) + tuple(q)] != want
+    assert wrong == 0
