@@ -520,8 +520,8 @@ ngf_status read_jds(ngf_ctx* c) {
     return NGF_OK;
 }
 
-// Autotune cache key: the device's architecture name, the image grid and
-// the deformation grid of a level.
+// Autotune cache key: the device's architecture name, the image grid, the
+// deformation grid and the kind of spacing of a level.
 std::string device_arch() {
     int dev = 0;
     hipDeviceProp_t prop{};
@@ -534,11 +534,19 @@ std::string device_arch() {
     if (colon != std::string::npos) a.resize(colon);
     return a.empty() ? "unknown" : a;
 }
-std::string tune_key(const Level& L) {
-    char buf[160];
-    std::snprintf(buf, sizeof(buf), "%s %d %d %d n%d,%d,%d", device_arch().c_str(), L.m[0],
-                  L.m[1], L.m[2], L.my[0], L.my[1], L.my[2]);
+// One key for the table in memory and the lines of the file.  It names the
+// generation of the kernels, since a variant's number outlives the kernel that was
+// timed under it, and whether every spacing is a power of two, which selects the
+// kernel's instance.  Lines of another generation are passed over.
+constexpr int kTuneGeneration = 2;
+std::string tune_key(const char* arch, const int m[3], const int my[3], bool pow2h) {
+    char buf[192];
+    std::snprintf(buf, sizeof(buf), "k%d %.63s %d %d %d n%d,%d,%d p%d", kTuneGeneration, arch,
+                  m[0], m[1], m[2], my[0], my[1], my[2], pow2h ? 1 : 0);
     return buf;
+}
+std::string tune_key(const Level& L) {
+    return tune_key(device_arch().c_str(), L.m, L.my, pow2(L.h[0]) && pow2(L.h[1]) && pow2(L.h[2]));
 }
 
 void tune_cache_load(ngf_ctx* c) {
@@ -546,14 +554,14 @@ void tune_cache_load(ngf_ctx* c) {
     if (!path) return;
     FILE* f = std::fopen(path, "r");
     if (!f) return;
-    char arch[64];
-    int m0, m1, m2, n0, n1, n2, v;
-    while (std::fscanf(f, "%63s %d %d %d n%d,%d,%d %d", arch, &m0, &m1, &m2, &n0, &n1, &n2,
-                       &v) == 8) {
-        if (v < 0 || v >= kNumVariants) continue;
-        char buf[160];
-        std::snprintf(buf, sizeof(buf), "%s %d %d %d n%d,%d,%d", arch, m0, m1, m2, n0, n1, n2);
-        c->tune_cache.emplace_back(buf, v);
+    char line[256], arch[64];
+    int gen, m[3], n[3], p, v;
+    while (std::fgets(line, sizeof(line), f)) {
+        if (std::sscanf(line, "k%d %63s %d %d %d n%d,%d,%d p%d %d", &gen, arch, m, m + 1, m + 2, n,
+                        n + 1, n + 2, &p, &v) != 10)
+            continue;
+        if (gen != kTuneGeneration || v < 0 || v >= kNumVariants) continue;
+        c->tune_cache.emplace_back(tune_key(arch, m, n, p != 0), v);
     }
     std::fclose(f);
 }
@@ -671,7 +679,7 @@ ngf_status autotune(ngf_ctx* c) {
         const std::string key = tune_key(L);
         int found = -1;
         for (auto& kv : c->tune_cache)
-            if (kv.first == key) found = kv.second;
+            if (kv.first == key && variant_ok(L, kv.second)) found = kv.second;
         if (found >= 0) {
             L.variant = found;
             if (is_gen(found)) need_rn(c, L);
