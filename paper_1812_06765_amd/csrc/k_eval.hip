@@ -443,8 +443,11 @@ void launch_image_tile(const ImagePassArgs& a, hipStream_t s) {
     }
 }
 
-template <int TX, int TY, int TZ, int RATIO>
-void launch_image_tile_atomic(const ImagePassArgs& a, hipStream_t s) {
+// the tile of kScatterVariant
+template <int RATIO>
+void launch_image_ratio_atomic(const ImagePassArgs& a, hipStream_t s) {
+    constexpr int TX = tile3d_x(kScatterVariant), TY = tile3d_y(kScatterVariant),
+                  TZ = tile3d_z(kScatterVariant);
     using L = ImageTile<TX, TY, TZ, RATIO>;
     const int blocks = a.ntx * a.nty * a.ntz;
     const size_t lds = sizeof(float) * L::LDS_FLOATS;
@@ -454,14 +457,6 @@ void launch_image_tile_atomic(const ImagePassArgs& a, hipStream_t s) {
     else
         hipLaunchKernelGGL((k_image_pass<TX, TY, TZ, RATIO, true, true, false>), dim3(blocks),
                            dim3(kThreads), lds, s, a);
-}
-
-template <int RATIO>
-void launch_image_ratio_atomic(const ImagePassArgs& a, int variant, hipStream_t s) {
-    if (variant == kTile3DSmall)
-        launch_image_tile_atomic<4, 8, 32, RATIO>(a, s);
-    else
-        launch_image_tile_atomic<kTX, kTY, kTZ, RATIO>(a, s);
 }
 
 template <int TX, int TY, int TZ, int RATIO>
@@ -518,11 +513,11 @@ void launch_image_pass_batch(const ImagePassArgs* args, const BlockRef* blk, int
         launch_image_ratio_batch<4>(args, blk, nblk, variant, pow2, s);
 }
 
-void launch_image_pass_atomic(const ImagePassArgs& a, int ratio, int variant, hipStream_t s) {
+void launch_image_pass_atomic(const ImagePassArgs& a, int ratio, hipStream_t s) {
     if (ratio == 2)
-        launch_image_ratio_atomic<2>(a, variant, s);
+        launch_image_ratio_atomic<2>(a, s);
     else if (ratio == 4)
-        launch_image_ratio_atomic<4>(a, variant, s);
+        launch_image_ratio_atomic<4>(a, s);
 }
 
 }  // namespace ngf

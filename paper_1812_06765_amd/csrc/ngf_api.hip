@@ -1024,7 +1024,7 @@ ngf_status eval_scatter(ngf_ctx* c, const Level& P, const float* R, const float*
     a.dpart = dpart;
     a.part = nullptr;
     if (want)
-        launch_image_pass_atomic(a, r, P.variant, c->stream);
+        launch_image_pass_atomic(a, r, c->stream);
     else
         launch_image_pass(a, r, P.variant, c->stream);
     HIPCHK(c, hipGetLastError());
