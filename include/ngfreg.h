@@ -338,9 +338,10 @@ ngf_status ngf_register_levels(ngf_ctx* ctx, float* y_out, ngf_report* rep);
  * corners k of its warp cell (the transpose of the trilinear warp, with
  * e = G^T v the NGF sensitivity of the warped template), summed per image
  * tile and added with float atomics, so it is reproducible only up to
- * rounding.  Where the scratch for e (one float per voxel) cannot be had, and
- * for 2^30 voxels and more, grad_y is scattered with atomics too.  Sec. 2.1 (Eq. 1),
- * Sec. 2.2 (Eq. 2 and the matrix-free chain rule).
+ * rounding.  Where the scratch for e (one float per voxel) cannot be had, for
+ * 2^30 voxels and more, and for small images (grad_T alone: below 3 * 2^16
+ * voxels; both at ratio 4: below 2^17) both are scattered with atomics by the
+ * image pass.  Sec. 2.1 (Eq. 1), Sec. 2.2 (Eq. 2 and the matrix-free chain rule).
  *   g, my      image grid; my[d] must be m[d]/ratio + 1 (else NGF_E_SHAPE)
  *   R, T, y    device inputs in the usual layouts
  *   gscale     device double multiplying both gradients (the upstream

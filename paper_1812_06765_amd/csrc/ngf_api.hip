@@ -953,12 +953,24 @@ ngf_status finish_J(ngf_ctx* c, const Results& to, double* J) {
     return NGF_OK;
 }
 
+// Whether the pair form is quicker with both gradients scattered by the image
+// pass: its four launches against five and a wait for each, where a template
+// gradient is wanted of a small image and grad_y is not, or costs few atomics.
+// Ratio 2 / 4, us through the entry point, scattered and not: grad_T alone of 32^3
+// 53 / 50 and 66 / 63, of 48^3 58 / 55 and 68 / 65, of 64^3 64 / 59 and 66 / 64 (a
+// deformation that expands by 20 % makes it 118 and 80); both gradients of 32^3 69 / 64 and 70 / 67, of 48^3 73 / 68 and 72 / 70, of 56^3
+// 78 / 72 and 72 / 70.
+bool scatter_is_quicker(const Level& P, bool want_y, bool want_T) {
+    if (!want_T) return false;
+    return want_y ? P.dyadic == 4 && P.N() < (int64_t{1} << 17) : P.N() < 3 * (int64_t{1} << 16);
+}
+
 // Differentiation form without the scatter of grad y: the evaluation's own
 // kernels (P^T as a gather), and grad_T from the sensitivities that the image
 // pass stores on the way (sens_room).  Forward and backward of 128^3 with both
-// gradients 282 -> 130 us; the scattering form (eval_scatter) remains for callers
-// who have no room for a value per voxel, and for grids beyond the marching
-// kernels' limits.
+// gradients 282 -> 130 us; the scattering form (eval_scatter) remains where it is
+// quicker, for callers who have no room for a value per voxel, and for grids beyond
+// the marching kernels' limits.
 ngf_status eval_diff(ngf_ctx* c, const Level& P, const float* R, const float* T, const float* y,
                      const double* gscale, double* J, double* J_dev, float* grad_y,
                      float* grad_T) {
@@ -1610,7 +1622,9 @@ ngf_status ngf_eval_pair(ngf_ctx* c, const ngf_grid* g, const int32_t my[3], con
     P.variant = kScatterVariant;  // the scatter form lives in a 3D-tile kernel
     P.dyadic = r;
     if (const ngf_status st = ensure_scratch(c, P); st != NGF_OK) return st;
-    if ((grad_y || grad_T) && march_fits(P) && (!grad_T || sens_room(c, P)))
+    if ((grad_y || grad_T) && march_fits(P) &&
+        !scatter_is_quicker(P, grad_y != nullptr, grad_T != nullptr) &&
+        (!grad_T || sens_room(c, P)))
         return eval_diff(c, P, R, T, y, gscale, J, J_dev, grad_y, grad_T);
     return eval_scatter(c, P, R, T, y, gscale, J, J_dev, grad_y, grad_T, nullptr);
 }
