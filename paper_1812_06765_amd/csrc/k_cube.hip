@@ -9,10 +9,9 @@
 // the two-voxel halo and the 96 edges between) each have a thread, which
 // warps it once; the index maps are in closed form instead of tables; P is
 // interpolated along x first, by the threads that load the nodes; and the
-// four stages are separated by four barriers.  Whole evaluations, against the
-// form that walked the halo in five rounds of 256 threads: 32^3 27.2 -> 20.5
-// us, 64 x 80 x 48 35.7 -> 28.5, 64^3 37.7 -> 30.5 (of which about 11 us are
-// the node pass and the reduction).
+// four stages are separated by four barriers.  Per launch, against the form that
+// walked the halo in five rounds of 256 threads (kernel trace): 32^3 14.2 -> 7.5
+// us, 64 x 80 x 48 22.8 -> 15.5, 64^3 22.6 -> 15.8.
 #include "ngf_internal.h"
 
 #include <math.h>

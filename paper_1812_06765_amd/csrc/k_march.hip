@@ -23,16 +23,18 @@
 // The P^T partial sums are written in the tile layout the node pass reads:
 // tile (chunk, ty, tz) owns node block [x0/R, x0/R + CX/R] x [...] x [...].
 //
-// What bounds it: vector instruction issue (76 % of the cycles at 256^3), of
-// which the float64 P and template index are the largest part.  Two rows of
+// What bounds it: vector instruction issue.  At 256^3 a voxel takes 228 vector
+// instructions, one of which issues in 60 % of the quad-cycles, and the float64 P
+// and template index, their largest part, take more than one each.  Two rows of
 // one node cell a thread share the z interpolations of P (21 float64
 // instructions a pair instead of 36), half the y neighbours and the y part of
 // P^T; the halo's positions and offsets stay packed in registers; values are
-// settled where they are formed so that 127 registers suffice without spills
-// (four waves per SIMD).  256^3, ratio 2, per launch: 162 us, 235 instructions
-// a voxel, against 233 us and 317 for the five-stage form with one voxel's
-// halves in different barriers that this replaced (ratio 4: 220 -> 140 us;
-// spacing 0.9: 253 -> 168 us).
+// settled where they are formed, so that 128 registers suffice (four waves per
+// SIMD): 127 and no spill at ratio 2, one spilled register in the 32 x 32 tile's
+// gradient forms at ratio 4 and in one of 16 x 64.  256^3, ratio 2, per launch
+// at a smooth deformation: 161 us, against 232 and 317 instructions for the
+// five-stage form with one voxel's halves in different barriers that this
+// replaced (ratio 4: 220 -> 140 us; spacing 0.9: 253 -> 168 us).
 #include "ngf_internal.h"
 
 #include <math.h>
@@ -768,7 +770,8 @@ int march_per_cu() {
 
 int image_march_slots(int ty, int tz) {
     // occupancy per CU, queried once per device and tile (the ratio-2
-    // instance stands for both ratios: same launch bounds, same LDS)
+    // instance stands for both ratios: its LDS is the larger, and either has
+    // four waves per SIMD)
     static std::atomic<int> cache[16][3];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0) dev = 0;

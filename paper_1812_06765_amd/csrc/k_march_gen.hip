@@ -35,8 +35,8 @@
 // along x of 64 planes are held a plane a lane and read by lane; dT and the
 // fractions are settled where they are formed, which keeps 121 registers from
 // spilling; cell and fraction come from one conversion and a median.
-// 191 x 203 x 157 on 64 x 68 x 53 nodes: evaluation 146 -> 128 us (spacings that
-// need a division 152 -> 132), J alone 95 -> 86.
+// 191 x 203 x 157 on 64 x 68 x 53 nodes, per launch (kernel trace): 126 -> 110 us,
+// with spacings that are no powers of two 133 -> 114.
 #include "ngf_internal.h"
 
 #include <math.h>

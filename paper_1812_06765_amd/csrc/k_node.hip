@@ -22,10 +22,9 @@
 // marches along x instead, with the x neighbours in registers
 // (node_march_body); the partial sums, 40 % of its traffic, bound it.
 //
-// Node pass and reduction of an evaluation, us, with the marching form at
-// every size and one component a workgroup, and now: 17^3 nodes 11.1 and 7.8,
-// 33^3 13.4 and 8.6, 49^3 14.5 and 10.5, 65^3 20.5 and 15.2, 129^3 46.6 and
-// 35.6.
+// Per launch, us (kernel trace), with the marching form at every size and one
+// component a workgroup, and now: 17^3 nodes 11.0 and 7.1, 33^3 12.3 and 7.6,
+// 64 x 68 x 53 15.5 and 14.2, 129^3 45.0 and 35.8.
 #include "ngf_internal.h"
 
 #include <math.h>

@@ -12,7 +12,8 @@
 // expanding or torn deformation) goes to memory directly.
 // A thread owns a (y, z) column of the tile and walks its SX planes, with y
 // interpolated in its column at the two node planes around x in registers, as
-// the standalone P does.
+// the standalone P does.  Its cells, fractions and sensitivities fill the 128
+// registers of two workgroups a CU and 5 to 7 more, which spill.
 // 128^3: 29 us, and 37 for the image pass that stores e, against 229 us for the
 // 3D-tile image pass that sends eight atomics a voxel to memory (102 us here
 // with float32 sums in LDS).

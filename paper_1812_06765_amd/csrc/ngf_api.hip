@@ -958,8 +958,8 @@ ngf_status finish_J(ngf_ctx* c, const Results& to, double* J) {
 // gradient is wanted of a small image and grad_y is not, or costs few atomics.
 // Ratio 2 / 4, us through the entry point, scattered and not: grad_T alone of 32^3
 // 53 / 50 and 66 / 63, of 48^3 58 / 55 and 68 / 65, of 64^3 64 / 59 and 66 / 64 (a
-// deformation that expands by 20 % makes it 118 and 80); both gradients of 32^3 69 / 64 and 70 / 67, of 48^3 73 / 68 and 72 / 70, of 56^3
-// 78 / 72 and 72 / 70.
+// deformation that expands by 20 % makes it 118 and 80); both gradients of 32^3
+// 69 / 64 and 70 / 67, of 48^3 73 / 68 and 72 / 70, of 56^3 78 / 72 and 72 / 70.
 bool scatter_is_quicker(const Level& P, bool want_y, bool want_T) {
     if (!want_T) return false;
     return want_y ? P.dyadic == 4 && P.N() < (int64_t{1} << 17) : P.N() < 3 * (int64_t{1} << 16);

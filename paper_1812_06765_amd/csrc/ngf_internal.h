@@ -221,7 +221,7 @@ struct ImagePassArgs {
     int cx;                // x chunk of the marching form (image planes)
     int px, py, pz;        // nodes per tile block of the P^T partial sums, per axis
     double hx, hy, hz;     // spacing (float64: continuous index of the warp)
-    double ihx, ihy, ihz;  // 1 / h, used only when every h is a power of two
+    double ihx, ihy, ihz;  // 1 / h (see index_of)
     int pow2h;             // 1: every spacing is a power of two (exact reciprocal)
     float fihx, fihy, fihz;        // 1 / h in float32
     float i2hx, i2hy, i2hz;        // 1 / (2 h)
@@ -256,7 +256,7 @@ struct NodePassArgs {
     float alpha;
     int want_grad;
     int gather;            // 1: sum the image-tile partials; 0: grad already holds grad D
-    const double* gscale;  // device scalar multiplying alpha grad S when gather == 0
+    const double* gscale;  // device scalar multiplying alpha grad S, and grad D where it is gathered
     const int* gate;       // as in ImagePassArgs
 };
 
