@@ -186,7 +186,7 @@ ngf_status ngf_set_node_grid(ngf_ctx* ctx, const int32_t my0[3]);
  * -1 = autotune (default:
  * at ngf_build_pyramid every level times each variant over three evaluations
  * at the identity and keeps the fastest, or the size rule's unless that is
- * more than 6 % behind it, here and in four further timings of both; choices are cached per image shape
+ * more than 6 % behind it, then and in six further timings of both; choices are cached per image shape
  * in the context and, if the environment variable NGF_TUNE_CACHE names a
  * file, appended to and read from that file); 0 = 3D tiles of 8x8x32 voxels
  * with a two-voxel halo; 1, 2, 3 = x-marching over 16x64 (y, z) tiles in

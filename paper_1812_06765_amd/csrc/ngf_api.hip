@@ -644,13 +644,13 @@ bool sens_room(ngf_ctx* c, const Level& L) {
 // Pick the image-pass variant of every level: forced, cached for this shape,
 // or the fastest of all variants over three timed evaluations at the identity
 // (whole evaluation: image pass, node pass and reduction).  The size rule's
-// variant is kept unless another is faster by more than kTuneMargin, and again so
-// by the least of kTuneAgain timings of both in turn: several come within a few
-// per cent of each other, one disturbed timing of three evaluations can be off by
-// more, and two contexts should not differ by it (of 18 pyramids of 256^3 under a
-// kernel trace 2 took another variant on some level by the first timing alone,
-// without the trace none).
-constexpr int kTuneAgain = 4;
+// variant is kept unless another is faster by more than kTuneMargin, and so in each
+// of kTuneAgain further timings of both in turn: several come within a few per
+// cent of each other, one disturbed timing of three evaluations can be off by more
+// (under a kernel trace, where the host is what small levels wait for, by half), and
+// two contexts should not differ by it.  Of 18 pyramids of 256^3 under a trace 2
+// took another variant on some level by the first timing alone; without, none.
+constexpr int kTuneAgain = 6;
 constexpr float kTuneMargin = 0.06f;
 ngf_status autotune(ngf_ctx* c) {
     if (c->forced_variant >= 0 || c->forced_variant == kVariantBySize) {
@@ -714,12 +714,9 @@ ngf_status autotune(ngf_ctx* c) {
             }
         }
         auto clear = [&] { return best_ms <= (1.0f - kTuneMargin) * rule_ms; };
-        if (best != rule && clear()) {
-            best_ms = rule_ms = 1e30f;
-            for (int k = 0; k < kTuneAgain && st == NGF_OK; ++k) {
-                rule_ms = std::min(rule_ms, time_variant(rule));
-                if (st == NGF_OK) best_ms = std::min(best_ms, time_variant(best));
-            }
+        for (int k = 0; k < kTuneAgain && st == NGF_OK && best != rule && clear(); ++k) {
+            rule_ms = time_variant(rule);
+            if (st == NGF_OK) best_ms = time_variant(best);
         }
         if (st == NGF_OK && !clear()) best = rule;
         L.variant = best;
