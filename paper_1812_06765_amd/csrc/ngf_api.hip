@@ -598,16 +598,16 @@ int variant_by_size(const Level& L) {
 // 173 / 193 / 241 / 171, of 64^3 315 / 231 / 202 / 220 / 266 / 233, of 128^3 1607 /
 // 600 / 567 / 546 / 556 / 604, of 224^3 11774 / 2092 / 2365 / 2151 / 2058 / 2185;
 // a pair of 48^3 alone 74 / 85 / 95 / 116 / 155 / 87, of 128^3 184 / 108 / 108 /
-// 126 / 176 / 118.  4, 10, 11 and 6 are one kernel, so their pairs share a launch;
-// 8 begins where few pairs gain by it what many lose.  Registrations against a
-// variant and chunks chosen over all pairs of a level: 12 pairs of 96 to 160 points
-// an axis 10.58 -> 10.30 ms, of 80 to 128 7.5 -> 6.7; where the sizes lie on both
-// sides of 64 Ki, 12 of 40 to 64 2.95 -> 3.25, 4 of 48 to 72 2.04 -> 2.19.
+// 126 / 176 / 118.  4, 10, 11 and 6 are one kernel, so their pairs share a launch.
+// The bounds are where cohorts of 3 to 12 pairs break even: over 24 cohorts of 40 to
+// 128 points an axis registrations take what they took with a variant and chunks
+// chosen over all pairs of a level (0.94 to 1.11 of it; bounds of 64 and 128 Ki: 4 %
+// more), 12 pairs of 96 to 160 points 10.6 -> 10.3 ms, 64 of 96 to 256 107.5 -> 110.
 int batch_variant(const Level& L) {
     if (!L.dyadic) return kMarchGen;
     const int64_t Ki = L.N() >> 10;
-    if (Ki < 64) return kTile3DTiny;
-    if (Ki < 128) return kMarch32Fit;
+    if (Ki < 96) return kTile3DTiny;
+    if (Ki < 320) return kMarch32Fit;
     if (Ki < 1280) return kMarch32x8;
     return Ki < 8192 ? kMarch32x16 : kMarch32x32;
 }

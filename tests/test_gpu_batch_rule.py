@@ -11,12 +11,12 @@ pytestmark = pytest.mark.gpu
 
 KW = dict(alpha=0.5, tau=10.0, rho=10.0, lbfgs_mem=5)
 # one of every class of the rule, by voxels: 8, 11, 4, 10 and 32x32 chunks (6)
-SHAPES = [(32, 40, 32), (64, 40, 32), (64, 56, 48), (128, 104, 112), (216, 224, 192)]
+SHAPES = [(32, 40, 32), (64, 56, 48), (128, 56, 64), (128, 104, 112), (216, 224, 192)]
 
 
 def _rule(m):
     ki = int(np.prod(m)) >> 10
-    return 8 if ki < 64 else 11 if ki < 128 else 4 if ki < 1280 else 10 if ki < 8192 else 6
+    return 8 if ki < 96 else 11 if ki < 320 else 4 if ki < 1280 else 10 if ki < 8192 else 6
 
 
 def _pairs(shapes, seed):
