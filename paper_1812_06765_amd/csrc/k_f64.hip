@@ -24,7 +24,7 @@
 // The voxel kernels walk along x: a thread owns one (y, z) position of the image
 // plane (taken flat), whose index maps it looks up once, and cx planes.  The
 // grid has a wave for every few planes, since each is a chain of dependent
-// loads.  128 x 112 x 96: k64_warp 21 us, k64_ngf 15 and k64_gather 33, against 37
+// loads.  128 x 112 x 96: k64_warp 22 us, k64_ngf 16 and k64_gather 34, against 37
 // + 9, 19 and 79 as kernels with a thread a voxel or node that looked its place
 // and every weight up by 64-bit divisions.
 #include <hip/hip_runtime.h>
