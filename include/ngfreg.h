@@ -483,7 +483,7 @@ ngf_status ngf_set_faults(ngf_ctx* ctx, int32_t flags);
  *     launches (each covering all pairs through a block table), captured as
  *     a hipGraph and replayed on the batch's own stream until every pair's
  *     level has ended.  Image-pass variants by each pair's own level size
- *     (below 96 Ki voxels 8, below 320 Ki 11, below 1280 Ki 4, below 8 Mi 10,
+ *     (below 96 Ki voxels 8, below 320 Ki 11, below 1280 Ki 4, below 4 Mi 10,
  *     else 6); ngf_batch_set_kernel overrides (the timed selection then takes one
  *     table shared by the pairs).
  *   1 threads: a host scheduler hands pairs, largest voxel count first, to

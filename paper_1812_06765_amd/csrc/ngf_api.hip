@@ -602,14 +602,14 @@ int variant_by_size(const Level& L) {
 // The bounds are where cohorts of 3 to 12 pairs break even: over 24 cohorts of 40 to
 // 128 points an axis registrations take what they took with a variant and chunks
 // chosen over all pairs of a level (0.94 to 1.11 of it; bounds of 64 and 128 Ki: 4 %
-// more), 12 pairs of 96 to 160 points 10.6 -> 10.3 ms, 64 of 96 to 256 107.5 -> 110.
+// more), 12 pairs of 96 to 160 points 10.6 -> 10.3 ms, 64 of 96 to 256 107.7 -> 109.0.
 int batch_variant(const Level& L) {
     if (!L.dyadic) return kMarchGen;
     const int64_t Ki = L.N() >> 10;
     if (Ki < 96) return kTile3DTiny;
     if (Ki < 320) return kMarch32Fit;
     if (Ki < 1280) return kMarch32x8;
-    return Ki < 8192 ? kMarch32x16 : kMarch32x32;
+    return Ki < 4096 ? kMarch32x16 : kMarch32x32;
 }
 
 // Image-pass variant of the differentiation form where the template gradient

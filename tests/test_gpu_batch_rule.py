@@ -16,7 +16,7 @@ SHAPES = [(32, 40, 32), (64, 56, 48), (128, 56, 64), (128, 104, 112), (216, 224,
 
 def _rule(m):
     ki = int(np.prod(m)) >> 10
-    return 8 if ki < 96 else 11 if ki < 320 else 4 if ki < 1280 else 10 if ki < 8192 else 6
+    return 8 if ki < 96 else 11 if ki < 320 else 4 if ki < 1280 else 10 if ki < 4096 else 6
 
 
 def _pairs(shapes, seed):
