@@ -69,6 +69,7 @@ void dfree(void* p) {
 // one given up first; should it then not come back either, *p is null.
 template <class T>
 ngf_status regrow(ngf_ctx* c, T** p, size_t have, size_t need) {
+    const std::string before = c->err;
     T* q = nullptr;
     if (dalloc(c, &q, need) == NGF_OK) {
         dfree(*p);
@@ -77,7 +78,10 @@ ngf_status regrow(ngf_ctx* c, T** p, size_t have, size_t need) {
     }
     if (!*p || (c->faults & NGF_FAULT_ALLOC)) return NGF_E_OOM;
     dfree(*p);
-    if (dalloc(c, p, need) == NGF_OK) return NGF_OK;
+    if (dalloc(c, p, need) == NGF_OK) {
+        c->err = before;  // nothing failed for the caller
+        return NGF_OK;
+    }
     const std::string why = c->err;
     (void)dalloc(c, p, have);
     return fail(c, NGF_E_OOM, why);
