@@ -519,8 +519,8 @@ ngf_status ngf_batch_register(ngf_batch* b, int32_t npairs, const float* const* 
 
 /* The batched evaluation (Sec. 2.1, Eq. 1 and 2, applied pair by pair):
  * J and grad J of many pairs at given deformations, each stage one launch
- * covering all pairs (one image pass per image-pass variant in use, one node
- * pass, one reduction).  Every pair's J and gradient equal those of the
+ * covering all pairs (one image pass per kernel in use, one node pass per form
+ * in use, one reduction).  Every pair's J and gradient equal those of the
  * single-pair ngf_eval_J_grad with the same variant bit for bit.
  *   ngf_batch_build  builds the pyramids of npairs pairs (R[i], T[i]: device
  *                    float32 images of grids[i]) in the batch's pair
